@@ -86,7 +86,7 @@ def draw(rng):
     if dtype == "f32" or path == "int":
         cap //= 4
     if path == "step":
-        cap = min(cap, 4096)
+        cap = min(cap, 4096, 49152 // H)  # within the library's scratch in either type
     cap = max(C, min(cap, 65536 * C // 64))
     T = int(round(math.exp(rng.uniform(math.log(C), math.log(cap)))))
     B = rng.choice([1, 1, 1, 2, 3, 4, 7])

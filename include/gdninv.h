@@ -337,20 +337,25 @@ int gdn_chunk_inverse_neumann_i16_fused(const void* K, const float* beta, const 
  * dk = dv = 128, else GDN_ERR_UNSUPPORTED; any other mode GDN_ERR_PARAM),
  * W = T diag(beta e^g) K, U = T diag(beta) V, V_new = U - W S,
  * O = scale (diag(e^g) Q S + ((Q K^T) (.) D) V_new) with D_ij = e^{g_i - g_j}
- * for i >= j (else 0), S' = e^{g_last} S + K^T diag(e^{g_last - g}) V_new.
+ * for i >= j (else 0), S' = e^{g_last} S + K^T diag(e^{g_last - g}) V_new,
+ * evaluated with V_new = T diag(beta) X, X = V - diag(e^g) K S, as
+ * O = scale (diag(e^g) Q S + P' X), S' = e^{g_last} S + G X with the
+ * per-chunk products P' = ((Q K^T) (.) D) T diag(beta) and
+ * G = K^T diag(e^{g_last - g}) T diag(beta).
  * Q, K: [B, L, H, dk]; V, O: [B, L, H, dv], all in `dtype` (GDN_F32 or
  * GDN_BF16); beta, g: [B, L, H] fp32 as for gdn_build_A.  S0 (nullable:
  * zero state) and S_final (nullable: not written): [B, H, dk, dv] fp32;
  * S_final may be S0 itself (updated in place) but must not overlap it
  * otherwise.  bf16 mode rounds to bf16 every MFMA operand, including the
- * state where it multiplies W and Q and V_new where it multiplies P and K^T;
+ * state where it multiplies K and Q, and X, P' and G;
  * the state itself is carried in fp32.  workspace: device memory of at least
  * gdn_chunk_forward_workspace() bytes, owned by the caller, contents
  * undefined on return; it must not overlap any tensor argument.
  * C in {16, 32, 64} (GDN_ERR_UNSUPPORTED for 128).  L = 0 with B H > 0
  * copies S0 (or zeros) into S_final.  GDN_ERR_WORKSPACE if workspace_bytes
- * is too small.  Two launches on `stream`: every chunk in parallel, then one
- * wave per (batch, head, 16 value columns) walking the chunks in order. */
+ * is too small.  Two launches on `stream`: every chunk in parallel, then
+ * workgroups of one (batch, head) and 16 or 32 value columns walking the
+ * chunks in order. */
 int gdn_chunk_forward(const void* Q, const void* K, const void* V, const float* beta,
                       const float* g, const float* S0, void* O, float* S_final, void* workspace,
                       int64_t workspace_bytes, int B, int L, int H, int dk, int dv, int C, int N,

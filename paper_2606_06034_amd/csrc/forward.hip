@@ -123,21 +123,25 @@ __device__ __forceinline__ void chunk_inverse_int(const Pair<F> (&kp)[NB][DK / 3
   const float amax =
       __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(__ockl_wfred_max_f32(m))));
   const int e = INV == kInvInt16 ? i16::quant_exp(amax) : i8::quant_exp(amax);
-  iq::AccI<NB> Lr;
-#pragma unroll
-  for (int b = 0; b < nlower(NB); ++b)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) Lr.a[b][v] = -(int)rintf(ldexpf(G.a[b][v], -e));
-  iq::AccI<NB> Ti;
   int eT;
-  if constexpr (INV == kInvInt16)
+  if constexpr (INV == kInvInt16) {
+    iq::AccI<NB> Lr, Ti;
+#pragma unroll
+    for (int b = 0; b < nlower(NB); ++b)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) Lr.a[b][v] = -(int)rintf(ldexpf(G.a[b][v], -e));
     iq::int_engine<i16::I16Ops, NB, false, NC, SC>(Lr, e, N, S, Ti, eT);
-  else
-    iq::int_engine<i8::I8Ops, NB, false, NC, SC>(Lr, e, N, S, Ti, eT);
+#pragma unroll
+    for (int b = 0; b < nlower(NB); ++b) Tr.a[b] = __builtin_convertvector(Ti.a[b], f32x4);
+  } else {
+    Acc<NB> Lr;
+    i8::quantize_neg(Lr, G, e);
+    iq::int_engine<i8::I8Ops, NB, false, NC, SC>(Lr, e, N, S, Tr, eT);
+  }
 #pragma unroll
   for (int b = 0; b < nlower(NB); ++b)
 #pragma unroll
-    for (int v = 0; v < 4; ++v) Tr.a[b][v] = ldexpf((float)Ti.a[b][v], eT);
+    for (int v = 0; v < 4; ++v) Tr.a[b][v] = ldexpf(Tr.a[b][v], eT);
 }
 
 // VARLEN: packed sequences (B = 1, L = T tokens, chunk tables pk); a chunk's

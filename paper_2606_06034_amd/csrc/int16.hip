@@ -16,9 +16,10 @@
 // [-127, 127]) and a product of codes is four int8 MFMAs over the quad
 // fragments of intq.hpp (quads per limb, packed straight from the codes):
 //   X Y = 2^16 Xh Yh + 2^8 (Xh Yl + Xl Yh) + Xl Yl,
-// with 2^8 Xh Yh + (Xh Yl + Xl Yh) exact in int32 (|.| < 2^29) and the sum
-// exact in fp64 (|X Y| < C 2^30 <= 2^36).  Products and sums are held as
-// fp64 integers (exact below 2^53), codes as int32.
+// with 2^8 Xh Yh + (Xh Yl + Xl Yh) exact in int32 (|.| < 2^29) and |X Y| < C
+// 2^30 <= 2^36.  Codes are held as int32, products as int32 rounded to odd
+// (int16_ops.hpp), the products of the C = 128 merge and the few sums too wide
+// for that as fp64 integers (exact below 2^53).
 #include "chunk.hpp"
 #include "int128.hpp"
 #include "intq.hpp"
@@ -74,11 +75,11 @@ __device__ __forceinline__ void store_i16(const AccI<NB>& Tr, int eTo, int16_t* 
   }
 }
 
-// Two waves per SIMD (amdgpu_waves_per_eu): at C = 64 the engine needs more
-// than 256 registers, one wave per SIMD; held to 256 the compiler keeps
-// about 120 values in scratch memory, and the second wave hides more latency
-// than the scratch traffic costs (4 % less time on 32768 tiles; the one-launch
-// kernel, whose K loads compete with that traffic, is faster without it).
+// Two waves per SIMD (amdgpu_waves_per_eu): at C = 64 the engine would take 32
+// registers more than the 256 that allows; held to 256 the compiler keeps
+// about 80 values in scratch memory, most of them across the branches that
+// seldom run, and the second wave hides more latency than they cost (one
+// launch from K, 32768 tiles: 499 us against 646 us with one wave).
 template <int NB, bool PLAIN, int NC = -1, int SC = -1>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2)))
 void k_neumann_i16(const int16_t* __restrict__ Aq,
@@ -111,9 +112,12 @@ void k_neumann_i16(const int16_t* __restrict__ Aq,
 
 // The whole INT16 path for one chunk in one wave: A in fp32 from K, beta, g
 // (the values gdn_build_A writes), quantised in registers, then the integer
-// inverse.
+// inverse.  Bound by vector operations: 32768 tiles of C = 64 in 514 us on
+// MI355X, against 885 us with products and sums as fp64 integers at one wave
+// per SIMD.
 template <int NB, int DK, typename F, typename TK, int NC = -1, int SC = -1>
-__global__ __launch_bounds__(64) void k_inverse_i16_fused(const TK* __restrict__ K,
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2)))
+void k_inverse_i16_fused(const TK* __restrict__ K,
                                                           const float* __restrict__ beta,
                                                           const float* __restrict__ g,
                                                           int16_t* __restrict__ Tq,

@@ -1,8 +1,9 @@
 // int16_ops.hpp -- the INT16 arithmetic of the integer inverse (Section 3.5,
-// Appendix G of arXiv 2606.06034): 16-bit codes as two int8 limbs, exact
-// products in fp64, quantisation by the scale rule of intq.hpp, exact fp64
-// sums and the I16Ops width the shared engine (int_engine of intq.hpp) runs
-// on, plus the per-tile quantiser's exponent.  Used by int16.hip and by the
+// Appendix G of arXiv 2606.06034): 16-bit codes as two int8 limbs, products and
+// sums in int32 rounded to odd (or in fp64 where the terms lie too far apart),
+// quantisation by the scale rule of intq.hpp and the I16Ops width the shared
+// engine (int_engine of intq.hpp) runs on, plus the per-tile quantiser's
+// exponent.  Used by int16.hip and by the
 // layer forward's integer-inverse mode.
 #pragma once
 
@@ -23,14 +24,10 @@ template <int NB> struct ColL { ColQ<NB> h, l; };
 // byte 0 of c, and c + 128 = 256 h + (l + 128) with 0 <= l + 128 <= 255, so
 // h's byte is byte 1 of c + 128.  Four codes of a block give one dword of a
 // quad per limb.
-__device__ __forceinline__ int pack_lo(i32x4 c) {
-  return (int)(((uint32_t)c[0] & 0xffu) | (((uint32_t)c[1] & 0xffu) << 8) |
-               (((uint32_t)c[2] & 0xffu) << 16) | ((uint32_t)c[3] << 24));
-}
+__device__ __forceinline__ int pack_lo(i32x4 c) { return gather_bytes<0>(c[0], c[1], c[2], c[3]); }
 __device__ __forceinline__ int pack_hi(i32x4 c) {
   const i32x4 u = c + 128;
-  return (int)((((uint32_t)u[0] >> 8) & 0xffu) | ((uint32_t)u[1] & 0xff00u) |
-               (((uint32_t)u[2] & 0xff00u) << 8) | (((uint32_t)u[3] & 0xff00u) << 16));
+  return gather_bytes<1>(u[0], u[1], u[2], u[3]);
 }
 
 // limb quads of the blocks that can meet [lo, hi] (others zero), row form
@@ -58,103 +55,114 @@ __device__ __forceinline__ void to_coll(ColL<NB>& Y, const AccI<NB>& D, int lo, 
     }
 }
 
-// D = X Y exactly, blocks outside [olo, ohi] set to 0; OUTQ: row-form result
-template <int NB, bool OUTQ>
-__device__ __forceinline__ void mml(AccD<NB>& D, const RowL<NB>& X, const ColL<NB>& Y, int olo,
-                                    int ohi) {
+// The limb products of one block of X Y (row-form result): X Y = 2^16 hh +
+// 2^8 mx + ll.
+struct LimbBlock { i32x4 hh, mx, ll; };
+template <int NB>
+__device__ __forceinline__ LimbBlock limb_block(const RowL<NB>& X, const ColL<NB>& Y, int I, int J) {
+  const i32x4 xh = X.h.r[I].v, xl = X.l.r[I].v, yh = Y.h.c[J].v, yl = Y.l.c[J].v, z = zero_i4();
+  LimbBlock b;
+  b.hh = __builtin_amdgcn_mfma_i32_16x16x64_i8(yh, xh, z, 0, 0, 0);
+  b.mx = __builtin_amdgcn_mfma_i32_16x16x64_i8(yl, xh, z, 0, 0, 0);
+  b.mx = __builtin_amdgcn_mfma_i32_16x16x64_i8(yh, xl, b.mx, 0, 0, 0);
+  b.ll = __builtin_amdgcn_mfma_i32_16x16x64_i8(yl, xl, z, 0, 0, 0);
+  return b;
+}
+// A product as fp64 integers, formed block by block where it is read (the
+// term of an exact_sum).
+template <int NB>
+struct LazyProd {
+  struct Blocks {
+    const RowL<NB>* X;
+    const ColL<NB>* Y;
+    __device__ __forceinline__ f64x4 operator[](int b) const {
+      int I = 0;
+      while ((I + 1) * (I + 2) / 2 <= b) ++I;
+      // the operand is opaque, so that each pass forms the block anew: kept
+      // from one pass to the next, ten blocks would take 80 registers
+      RowL<NB> x = *X;
+      asm volatile("" : "+v"(x.h.r[I].v), "+v"(x.l.r[I].v));
+      const LimbBlock p = limb_block(x, *Y, I, b - I * (I + 1) / 2);
+      f64x4 r;
 #pragma unroll
-  for (int I = 0; I < NB; ++I)
-#pragma unroll
-    for (int J = 0; J <= I; ++J) {
-      f64x4 r = f64x4{0.0, 0.0, 0.0, 0.0};
-      if (blk_nz(I - J, olo, ohi)) {
-        const i32x4 xh = X.h.r[I].v, xl = X.l.r[I].v, yh = Y.h.c[J].v, yl = Y.l.c[J].v;
-        const i32x4 z = zero_i4();
-        i32x4 hh, mx, ll;
-        if constexpr (OUTQ) {
-          hh = __builtin_amdgcn_mfma_i32_16x16x64_i8(yh, xh, z, 0, 0, 0);
-          mx = __builtin_amdgcn_mfma_i32_16x16x64_i8(yl, xh, z, 0, 0, 0);
-          mx = __builtin_amdgcn_mfma_i32_16x16x64_i8(yh, xl, mx, 0, 0, 0);
-          ll = __builtin_amdgcn_mfma_i32_16x16x64_i8(yl, xl, z, 0, 0, 0);
-        } else {
-          hh = __builtin_amdgcn_mfma_i32_16x16x64_i8(xh, yh, z, 0, 0, 0);
-          mx = __builtin_amdgcn_mfma_i32_16x16x64_i8(xh, yl, z, 0, 0, 0);
-          mx = __builtin_amdgcn_mfma_i32_16x16x64_i8(xl, yh, mx, 0, 0, 0);
-          ll = __builtin_amdgcn_mfma_i32_16x16x64_i8(xl, yl, z, 0, 0, 0);
-        }
-#pragma unroll
-        for (int v = 0; v < 4; ++v)
-          r[v] = __builtin_fma((double)(hh[v] * 256 + mx[v]), 256.0, (double)ll[v]);
-      }
-      D.a[bidx(I, J)] = r;
+      for (int v = 0; v < 4; ++v)
+        r[v] = __builtin_fma((double)(p.hh[v] * 256 + p.mx[v]), 256.0, (double)p.ll[v]);
+      return r;
     }
-}
+  } a;
+};
 
-// codes of the limb matrices recombined: D = 256 H + L
+// A product in int32.  An entry F = X Y (below 2^36) is kept as F / 128
+// rounded to odd: J = 2 floor(F / 256) + (256 does not divide F), below 2^30.
+// J and F / 128 lie on the same side of every even integer (and meet one only
+// together), so they compare alike with, and round half to even alike to,
+// every quantum 2^s with s >= 2, and so do their sums with even integers.
+// Half the registers of fp64 integers, which is what lets two waves share a
+// SIMD.
 template <int NB>
-__device__ __forceinline__ void join(AccI<NB>& D, const AccI<NB>& H, const AccI<NB>& L) {
+__device__ __forceinline__ i32x4 odd_block(const RowL<NB>& X, const ColL<NB>& Y, int I, int J) {
+  const i32x4 xh = X.h.r[I].v, xl = X.l.r[I].v, yh = Y.h.c[J].v, yl = Y.l.c[J].v, z = zero_i4();
+  const i32x4 ll = __builtin_amdgcn_mfma_i32_16x16x64_i8(yl, xl, z, 0, 0, 0);
+  const i32x4 hh = __builtin_amdgcn_mfma_i32_16x16x64_i8(yh, xh, z, 0, 0, 0);
+  i32x4 f = (hh << 8) + (ll >> 8);  // floor(F / 256), completed by the mixed products
+  f = __builtin_amdgcn_mfma_i32_16x16x64_i8(yl, xh, f, 0, 0, 0);
+  f = __builtin_amdgcn_mfma_i32_16x16x64_i8(yh, xl, f, 0, 0, 0);
+  i32x4 r;
 #pragma unroll
-  for (int b = 0; b < nlower(NB); ++b) D.a[b] = H.a[b] * 256 + L.a[b];
+  for (int v = 0; v < 4; ++v) r[v] = (f[v] << 1) | (int)min((uint32_t)(ll[v] & 255), 1u);
+  return r;
+}
+// y 2^-t rounded to odd (t >= 1): floor, with the last bit set when bits were
+// lost; composes with what is rounded to odd already
+__device__ __forceinline__ i32x4 odd_shift(i32x4 y, int t) {
+  const uint32_t mask = (1u << t) - 1;
+  i32x4 r;
+#pragma unroll
+  for (int v = 0; v < 4; ++v)
+    r[v] = (y[v] >> t) | (int)min((uint32_t)y[v] & mask, 1u);
+  return r;
+}
+// the product itself, for |F| < 2^31
+template <int NB>
+__device__ __forceinline__ i32x4 exact_block(const RowL<NB>& X, const ColL<NB>& Y, int I, int J) {
+  const LimbBlock p = limb_block(X, Y, I, J);
+  return (p.hh << 16) + (p.mx << 8) + p.ll;
 }
 
-// Form changes through the identity, limb by limb (exact).
-// Column-form limbs (and, when wanted, codes) of a row-form matrix.
+// Column-form limbs of a row-form matrix, through the identity (exact).
 template <int NB>
-__device__ __forceinline__ void row_to_col(ColL<NB>& Y, AccI<NB>* codes, const RowL<NB>& X,
-                                           const ColQ<NB>& Ic, int lo, int hi) {
-  AccI<NB> h, l;
-  mmi<NB, false>(h, X.h, Ic, lo, hi);
-  mmi<NB, false>(l, X.l, Ic, lo, hi);
-  to_colq(Y.h, h, lo, hi);
-  to_colq(Y.l, l, lo, hi);
-  if (codes) join(*codes, h, l);
-}
-// Row-form codes of a column-form matrix.
-template <int NB>
-__device__ __forceinline__ void col_to_row(AccI<NB>& D, const RowQ<NB>& Iq, const ColL<NB>& Y,
+__device__ __forceinline__ void row_to_col(ColL<NB>& Y, const RowL<NB>& X, const ColQ<NB>& Ic,
                                            int lo, int hi) {
-  AccI<NB> h, l;
-  mmi<NB, true>(h, Iq, Y.h, lo, hi);
-  mmi<NB, true>(l, Iq, Y.l, lo, hi);
-  join(D, h, l);
+  AccI<NB> t;
+  mmi<NB, false>(t, X.h, Ic, lo, hi);
+  to_colq(Y.h, t, lo, hi);
+  mmi<NB, false>(t, X.l, Ic, lo, hi);
+  to_colq(Y.l, t, lo, hi);
 }
 
-// a product (fp64 integers, exact) of exponent e_in to codes q by the scale
-// rule over the band blocks (other blocks 0); exponent and non-zero flag
-// through refs.  The wave maximum is taken over the high dwords of |x|
-// (shift_canon_hi).
+// D 2^-s, in place: a right shift by s > 0 rounded half to even (|y| + 2^(s -
+// 1) stays below 2^31), or an exact left shift
 template <int NB>
-__device__ __forceinline__ void requant(const AccD<NB>& D, AccI<NB>& q, int lo, int hi, int e_in,
-                                        int& e_out, bool& nz) {
-  int m = 0;
+__device__ __forceinline__ void rescale_i32(AccI<NB>& D, int s, int lo, int hi) {
+  auto each = [&](auto&& f) {
 #pragma unroll
-  for (int I = 0; I < NB; ++I)
+    for (int I = 0; I < NB; ++I)
 #pragma unroll
-    for (int J = 0; J <= I; ++J)
-      if (blk_nz(I - J, lo, hi))
+      for (int J = 0; J <= I; ++J)
+        if (blk_nz(I - J, lo, hi))
 #pragma unroll
-        for (int v = 0; v < 4; ++v) m = max(m, __double2hiint(fabs(D.a[bidx(I, J)][v])));
-  const int amax_hi = wave_max(m);
-  nz = amax_hi > 0;
-  const int s = nz ? shift_canon_hi<kQmax, 15>(amax_hi) : 0;
-  const double sc = ldexp(1.0, -s);
-#pragma unroll
-  for (int I = 0; I < NB; ++I)
-#pragma unroll
-    for (int J = 0; J <= I; ++J) {
-      i32x4 r = zero_i4();
-      if (blk_nz(I - J, lo, hi))
-#pragma unroll
-        for (int v = 0; v < 4; ++v) r[v] = rne_scaled(D.a[bidx(I, J)][v], sc);
-      q.a[bidx(I, J)] = r;
-    }
-  e_out = nz ? e_in + s : 0;
+          for (int v = 0; v < 4; ++v) D.a[bidx(I, J)][v] = f(D.a[bidx(I, J)][v]);
+  };
+  if (s > 0) {
+    const int h = (1 << (s - 1)) - 1;
+    each([&](int y) { return (y + h + ((y >> s) & 1)) >> s; });
+  } else if (s < 0) {
+    each([&](int y) { return y << -s; });
+  }
 }
 
 // exact int32 values (|y| < 2^30) of exponent e_in to codes by the scale
-// rule, in place: a right shift by s > 0 rounded half to even (the sum
-// y + 2^(s-1) stays below 2^31), or an exact left shift; exponent and
-// non-zero flag through refs
+// rule, in place; exponent and non-zero flag through refs
 template <int NB>
 __device__ __forceinline__ void requant_i32(AccI<NB>& D, int lo, int hi, int e_in, int& e_out,
                                             bool& nz) {
@@ -165,17 +173,7 @@ __device__ __forceinline__ void requant_i32(AccI<NB>& D, int lo, int hi, int e_i
     return;
   }
   const int s = shift_canon<kQmax, 15>(amax);
-#pragma unroll
-  for (int I = 0; I < NB; ++I)
-#pragma unroll
-    for (int J = 0; J <= I; ++J)
-      if (blk_nz(I - J, lo, hi))
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const int y = D.a[bidx(I, J)][v];
-          D.a[bidx(I, J)][v] =
-              s > 0 ? (y + (1 << (s - 1)) - 1 + ((y >> s) & 1)) >> s : y << (-s);
-        }
+  rescale_i32(D, s, lo, hi);
   e_out = e_in + s;
 }
 
@@ -205,11 +203,14 @@ __device__ __forceinline__ void canon(AccI<NB>& q, int lo, int hi, int& e, bool&
 // ---------------------------------------------------------------------------
 
 // The INT16 width for the shared integer engine (int_engine of intq.hpp):
-// limb quads, products as fp64 integers, sums exact in fp64.
+// limb quads, products and sums in int32 rounded to odd, or exact in fp64.
 template <int NB> struct I16Ops {
+  using Codes = AccI<NB>;
   using Row = RowL<NB>;
   using Col = ColL<NB>;
-  using Prod = AccD<NB>;
+  static __device__ __forceinline__ bool any(const Codes& D, int lo, int hi) {
+    return amax_of(D, lo, hi) > 0;
+  }
   static constexpr int kQ = kQmax;
   static constexpr int kQB = 15;                                      // |code| < 2^15
   static constexpr int kAccB = 30 + (NB == 1 ? 4 : NB == 2 ? 5 : 6);  // |product| < C 2^30
@@ -229,13 +230,84 @@ template <int NB> struct I16Ops {
                               ? unpack4(X.h.r[I].v[J]) * 256 + unpack4(X.l.r[I].v[J])
                               : zero_i4();
   }
-  template <bool OUTQ>
-  static __device__ __forceinline__ void mm(Prod& D, const Row& X, const Col& Y, int lo, int hi) {
-    mml<NB, OUTQ>(D, X, Y, lo, hi);
+  // the blocks f(I, J) of the band [lo, hi], the others 0
+  template <typename Fn>
+  static __device__ __forceinline__ void blocks(AccI<NB>& D, int lo, int hi, Fn&& f) {
+#pragma unroll
+    for (int I = 0; I < NB; ++I)
+#pragma unroll
+      for (int J = 0; J <= I; ++J)
+        D.a[bidx(I, J)] = blk_nz(I - J, lo, hi) ? f(I, J) : zero_i4();
   }
-  static __device__ __forceinline__ void requant(const Prod& D, AccI<NB>& q, int lo, int hi,
-                                                 int e_in, int& e_out, bool& nz) {
-    i16::requant(D, q, lo, hi, e_in, e_out, nz);
+  // q(X Y 2^e_in) over [lo, hi] as codes and as row fragments (X and Y are
+  // read before qr is written).  Rounded to odd at 1 / 128 when the shift from
+  // there is at least 2 (a maximum of 2^16 or more); a smaller product is below
+  // 2^23 and formed in int32 as it is.
+  static __device__ __forceinline__ void mulq(const Row& X, const Col& Y, int lo, int hi, int e_in,
+                                              Codes& q, Row& qr, int& e_out, bool& nz) {
+    blocks(q, lo, hi, [&](int I, int J) { return odd_block(X, Y, I, J); });
+    int amax = amax_of(q, lo, hi), e = e_in + 7;
+    if (amax < (1 << 16)) {
+      blocks(q, lo, hi, [&](int I, int J) { return exact_block(X, Y, I, J); });
+      amax = amax_of(q, lo, hi);
+      e = e_in;
+    }
+    nz = amax > 0;
+    const int s = nz ? shift_canon<kQmax, 15>(amax) : 0;
+    rescale_i32(q, s, lo, hi);
+    e_out = nz ? e + s : 0;
+    to_rowl(qr, q, lo, hi);
+  }
+  // out = q(x + y + sign X Y 2^ep), the product on the sub-diagonals from plo
+  // on and absent when !pp.  In int32: the product, rounded to odd at 1 / 128
+  // (units of 2^(ep + 7)), and the terms that are even integers below 2^29
+  // there; then that sum rounded to odd t bits higher, so that the coarsest
+  // term stays below 2^29, and the terms that are even integers from there on.
+  // Valid when every term falls on one side and the final shift is at least 2;
+  // else exactly in fp64.
+  static __device__ __forceinline__ void mul_sum(Codes& out, int& eo, bool& nz,
+                                                 const Term<Codes>& x, const Term<Codes>& y,
+                                                 const Row& X, const Col& Y, int ep, int sign,
+                                                 int plo, bool pp, int lo, int hi) {
+    const int kx = x.p ? x.e - ep - 7 : 1, ky = y.p ? y.e - ep - 7 : 1;  // absent: zero codes
+    const int t = max(0, max(kx, ky) - 14);
+    const bool cx = kx - t >= 1, cy = ky - t >= 1;  // coarse: even at the coarser unit
+    if (pp && t <= 30 && (cx || (kx >= 1 && kx <= 14)) && (cy || (ky >= 1 && ky <= 14))) {
+      AccI<NB> r;
+      // a term's shift before and after the rounding (32: not there)
+      auto put = [&](i32x4& a, const Term<Codes>& q, int m, int b, int k) {
+        if (blk_nz(m, q.lo, q.hi)) a += (q.t->a[b] * q.sign) << k;
+      };
+      blocks(r, lo, hi, [&](int I, int J) {
+        i32x4 a = zero_i4();
+        if (blk_nz(I - J, plo, hi)) a = odd_block(X, Y, I, J);
+        return sign < 0 ? -a : a;
+      });
+      auto add_term = [&](const Term<Codes>& q, int k) {
+        blocks(r, lo, hi, [&](int I, int J) {
+          i32x4 a = r.a[bidx(I, J)];
+          put(a, q, I - J, bidx(I, J), k);
+          return a;
+        });
+      };
+      if (!cx) add_term(x, kx);
+      if (!cy) add_term(y, ky);
+      if (t > 0)
+        blocks(r, lo, hi, [&](int I, int J) { return odd_shift(r.a[bidx(I, J)], t); });
+      if (cx) add_term(x, kx - t);
+      if (cy) add_term(y, ky - t);
+      const int amax = amax_of(r, lo, hi);
+      if (amax >= (1 << 16)) {
+        const int s = shift_canon<kQmax, 15>(amax);
+        rescale_i32(r, s, lo, hi);
+        out = r;
+        eo = ep + 7 + t + s;
+        nz = true;
+        return;
+      }
+    }
+    LazyProd<NB> D{{&X, &Y}};
+    exact_sum<kQ, kQB, NB>(out, eo, nz, x, y, term(D, ep, kAccB, sign, plo, hi, pp), lo, hi);
   }
   static __device__ __forceinline__ void canon(AccI<NB>& q, int lo, int hi, int& e, bool& nz) {
     i16::canon(q, lo, hi, e, nz);
@@ -244,18 +316,21 @@ template <int NB> struct I16Ops {
   // [ylo, hi]); Y is at the finest scale that holds it, and so is X when
   // xc.  Exponents 2 QB + 3 or more apart: the finer term is below an
   // eighth of the output quantum and leaves the coarser's codes as they are
-  // (at their finest scale); at most QB apart: the aligned sum is below
-  // 32639 (2^15 + 1) < 2^30 and exact in int32, and so is its rounding;
-  // otherwise the sum is exact in fp64 (below 2^48).  Every path gives the
-  // exact sum quantised once by the scale rule.
+  // (at their finest scale); at most 14 apart: the aligned sum is below
+  // 32639 (2^14 + 1) < 2^30 and exact in int32, and so is its rounding;
+  // between: the finer term rounded to odd at the unit 14 bits under the
+  // coarser one's, where the coarser is an even integer of 2^27 or more at its
+  // maximum, so the rounding that follows shifts by 12 or more and comes out
+  // as that of the exact sum.
   static __device__ __forceinline__ void add(AccI<NB>& X, int& eX, bool& nzX, int xlo, bool xc,
                                              const AccI<NB>& Y, int eY, bool nzY, int ys, int ylo,
                                              int lo, int hi) {
-    const int g = !nzY ? 64 : nzX ? eX - eY : -64;
-    if (g >= 2 * kQB + 3) {
-      if (!xc) canon(X, xlo, hi, eX, nzX);
-      return;
+    int g = !nzY ? 64 : nzX ? eX - eY : -64;
+    if (!xc && g > 14) {
+      canon(X, xlo, hi, eX, nzX);
+      if (nzY && nzX) g = eX - eY;
     }
+    if (g >= 2 * kQB + 3) return;
     if (g <= -(2 * kQB + 3)) {
 #pragma unroll
       for (int I = 0; I < NB; ++I)
@@ -267,31 +342,34 @@ template <int NB> struct I16Ops {
       nzX = true;
       return;
     }
-    if (g >= -kQB && g <= kQB) {
-      const int gx = max(g, 0), gy = max(-g, 0);
-      const int e0 = min(eX, eY);
+    auto each = [&](auto&& f) {
 #pragma unroll
       for (int I = 0; I < NB; ++I)
 #pragma unroll
         for (int J = 0; J <= I; ++J)
-          if (blk_nz(I - J, lo, hi)) {
-            i32x4 x = blk_nz(I - J, xlo, hi) ? X.a[bidx(I, J)] : zero_i4();
-            const i32x4 y = blk_nz(I - J, ylo, hi) ? Y.a[bidx(I, J)] : zero_i4();
-#pragma unroll
-            for (int v = 0; v < 4; ++v) x[v] = (x[v] << gx) + ys * (y[v] << gy);
-            X.a[bidx(I, J)] = x;
-          }
-      requant_i32(X, lo, hi, e0, eX, nzX);
-      return;
+          if (blk_nz(I - J, lo, hi))
+            X.a[bidx(I, J)] = f(blk_nz(I - J, xlo, hi) ? X.a[bidx(I, J)] : zero_i4(),
+                                blk_nz(I - J, ylo, hi) ? Y.a[bidx(I, J)] * ys : zero_i4());
+    };
+    int e0;
+    if (g > 14) {
+      each([&](i32x4 x, i32x4 y) { return (x << 14) + odd_shift(y, g - 14); });
+      e0 = eX - 14;
+    } else if (g >= 0) {
+      each([&](i32x4 x, i32x4 y) { return (x << g) + y; });
+      e0 = eY;
+    } else if (g >= -14) {
+      each([&](i32x4 x, i32x4 y) { return (y << -g) + x; });
+      e0 = eX;
+    } else {
+      each([&](i32x4 x, i32x4 y) { return (y << 14) + odd_shift(x, -g - 14); });
+      e0 = eY - 14;
     }
-    AccI<NB> out;
-    exact_sum<kQ, kQB, NB>(out, eX, nzX, term(X, eX, kQB, 1, xlo, hi, nzX),
-                           term(Y, eY, kQB, ys, ylo, hi, nzY), no_term(Y), lo, hi);
-    X = out;
+    requant_i32(X, lo, hi, e0, eX, nzX);
   }
   static __device__ __forceinline__ void row_to_col(Col& Y, const Row& X, const ColQ<NB>& Ic,
                                                     int lo, int hi) {
-    i16::row_to_col<NB>(Y, nullptr, X, Ic, lo, hi);
+    i16::row_to_col<NB>(Y, X, Ic, lo, hi);
   }
 };
 

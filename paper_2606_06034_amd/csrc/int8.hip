@@ -12,7 +12,7 @@
 //   * every operator of Algorithm 1 (MatMul, Add, the residual
 //     E = I - (I + A) T0) is evaluated exactly from its operands' codes
 //     (int8 x int8 products exact in int32 on v_mfma_i32_16x16x64_i8, sums
-//     exact in int32 or fp64) and its result quantised once;
+//     exact in fp32 or fp64) and its result quantised once;
 //   * T0 is masked once after its sum; the residual powers are
 //     P_s = P_{s-1} E; T_hat = T0 T;
 //   * split form: the unit diagonal of T0, T and T_hat stays out of the
@@ -35,7 +35,7 @@ namespace i8 {
 // optionally Tdeq = T_hat in fp32 (I + Tq 2^eT in split form, Tq 2^eT in
 // plain form) for tile `tile`
 template <int NB, bool PLAIN = false>
-__device__ __forceinline__ void store_i8(const AccI<NB>& Tr, int eTo, int8_t* __restrict__ Tq,
+__device__ __forceinline__ void store_i8(const Acc<NB>& Tr, int eTo, int8_t* __restrict__ Tq,
                                          int32_t* __restrict__ eT, float* __restrict__ Tdeq,
                                          int64_t tile) {
   constexpr int C = 16 * NB;
@@ -45,7 +45,7 @@ __device__ __forceinline__ void store_i8(const AccI<NB>& Tr, int eTo, int8_t* __
   for (int I = 0; I < NB; ++I)
 #pragma unroll
     for (int J = 0; J < NB; ++J)
-      *(int*)(t + (I * 16 + c) * C + J * 16 + 4 * g) = J <= I ? pack4(Tr.a[bidx(I, J)]) : 0;
+      *(int*)(t + (I * 16 + c) * C + J * 16 + 4 * g) = J <= I ? packf(Tr.a[bidx(I, J)]) : 0;
   if (lane_id() == 0) eT[tile] = eTo;
   if (Tdeq) {
     float* td = Tdeq + tile * (C * C);
@@ -57,7 +57,7 @@ __device__ __forceinline__ void store_i8(const AccI<NB>& Tr, int eTo, int8_t* __
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
           const int d = 16 * (I - J) + c - 4 * g - v;
-          if (J <= I && d >= (PLAIN ? 0 : 1)) x[v] = ldexpf((float)Tr.a[bidx(I, J)][v], eTo);
+          if (J <= I && d >= (PLAIN ? 0 : 1)) x[v] = ldexpf(Tr.a[bidx(I, J)][v], eTo);
           if (!PLAIN && d == 0) x[v] = 1.f;
         }
         *(f32x4*)(td + (I * 16 + c) * C + J * 16 + 4 * g) = x;
@@ -65,8 +65,12 @@ __device__ __forceinline__ void store_i8(const AccI<NB>& Tr, int eTo, int8_t* __
   }
 }
 
+// Two waves per SIMD (amdgpu_waves_per_eu): at C = 64 the engine would take a
+// few registers more than the 256 that allows, and a wave alone issues a
+// vector operation in 58 % of its cycles.
 template <int NB, bool PLAIN, int NC = -1, int SC = -1>
-__global__ __launch_bounds__(64) void k_neumann_i8(const int8_t* __restrict__ Aq,
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2)))
+void k_neumann_i8(const int8_t* __restrict__ Aq,
                                                    const int32_t* __restrict__ eA,
                                                    int8_t* __restrict__ Tq,
                                                    int32_t* __restrict__ eT,
@@ -76,19 +80,17 @@ __global__ __launch_bounds__(64) void k_neumann_i8(const int8_t* __restrict__ Aq
   const int g = lane_g(), c = lane_c();
   const int8_t* a = Aq + tile * (C * C);
   // ---- Lm = -A (row form), strictly lower
-  AccI<NB> Lr;
+  Acc<NB> Lr;
 #pragma unroll
   for (int I = 0; I < NB; ++I)
 #pragma unroll
     for (int J = 0; J <= I; ++J) {
       const int w = *(const int*)(a + (I * 16 + c) * C + J * 16 + 4 * g);
-      i32x4 x = unpack4(w);
-#pragma unroll
-      for (int v = 0; v < 4; ++v) x[v] = drow(I - J, v) > 0 ? -x[v] : 0;
-      Lr.a[bidx(I, J)] = x;
+      const f32x4 x = __builtin_convertvector(unpack4(w), f32x4);
+      Lr.a[bidx(I, J)] = band_block<false>(-x, I - J, 1, C);
     }
   const int eL = __builtin_amdgcn_readfirstlane(eA[tile]);
-  AccI<NB> Tr;
+  Acc<NB> Tr;
   int eTo;
   int_engine<I8Ops, NB, PLAIN, NC, SC>(Lr, eL, Nrt, Srt, Tr, eTo);
   store_i8<NB, PLAIN>(Tr, eTo, Tq, eT, Tdeq, tile);
@@ -97,9 +99,12 @@ __global__ __launch_bounds__(64) void k_neumann_i8(const int8_t* __restrict__ Aq
 
 // The whole low-bit path for one chunk in one wave: A in fp32 from K, beta,
 // g (the same values gdn_build_A writes), quantised in registers by the
-// quantiser's rule, then the integer inverse.
+// quantiser's rule, then the integer inverse.  Bound by vector operations
+// (3.9 K a wave; 6.4 K with codes as int32): 32768 tiles of C = 64 in 241 to
+// 264 us on MI355X (the clock's state), 382 us before.
 template <int NB, int DK, typename F, typename TK, int NC = -1, int SC = -1>
-__global__ __launch_bounds__(64) void k_inverse_i8_fused(const TK* __restrict__ K,
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2)))
+void k_inverse_i8_fused(const TK* __restrict__ K,
                                                          const float* __restrict__ beta,
                                                          const float* __restrict__ g,
                                                          int8_t* __restrict__ Tq,
@@ -119,12 +124,8 @@ __global__ __launch_bounds__(64) void k_inverse_i8_fused(const TK* __restrict__ 
   const float amax =
       __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(__ockl_wfred_max_f32(m))));
   const int e = quant_exp(amax);
-  AccI<NB> Lr;
-#pragma unroll
-  for (int b = 0; b < nlower(NB); ++b)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) Lr.a[b][v] = -(int)rintf(ldexpf(G.a[b][v], -e));
-  AccI<NB> Tr;
+  Acc<NB> Lr, Tr;
+  quantize_neg(Lr, G, e);
   int eTo;
   int_engine<I8Ops, NB, false, NC, SC>(Lr, e, Nrt, Srt, Tr, eTo);
   store_i8<NB>(Tr, eTo, Tq, eT, Tdeq, ch.tile);
@@ -143,7 +144,7 @@ struct I8W : I8Ops<4> {
   template <int NC, int SC>
   static __device__ __forceinline__ void engine(const AccI<4>& Lr, int eL, int N, int S,
                                                 AccI<4>& Tr, int& eTo) {
-    int_engine<I8Ops, 4, false, NC, SC>(Lr, eL, N, S, Tr, eTo);
+    int_engine_i32<I8Ops, 4, false, NC, SC>(Lr, eL, N, S, Tr, eTo);
   }
   static __device__ __forceinline__ void to_frow(Row& X, const FullI& D) { to_rowq_full(X, D); }
   static __device__ __forceinline__ void frow_to_col(Col& Y, const Row& X, const ColQ<4>& Ic) {

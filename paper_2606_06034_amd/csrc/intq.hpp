@@ -17,6 +17,8 @@
 
 #include <stdint.h>
 
+#include <type_traits>
+
 // wave reductions of the ROCm device library
 extern "C" __device__ __attribute__((const)) int __ockl_wfred_max_i32(int);
 extern "C" __device__ __attribute__((const)) float __ockl_wfred_max_f32(float);
@@ -36,11 +38,16 @@ template <int NB> struct AccI { i32x4 a[nlower(NB)]; };
 
 __device__ __forceinline__ i32x4 zero_i4() { return i32x4{0, 0, 0, 0}; }
 
-// 4 int32 in [-128, 127] <-> 4 bytes (value v in byte v)
-__device__ __forceinline__ int pack4(i32x4 x) {
-  return (int)((uint32_t)(x[0] & 0xff) | ((uint32_t)(x[1] & 0xff) << 8) |
-               ((uint32_t)(x[2] & 0xff) << 16) | ((uint32_t)(x[3] & 0xff) << 24));
+// byte B of four dwords, one after another (two byte permutes and an or)
+template <int B>
+__device__ __forceinline__ int gather_bytes(int x0, int x1, int x2, int x3) {
+  constexpr uint32_t b = B;
+  const uint32_t lo = __builtin_amdgcn_perm((uint32_t)x1, (uint32_t)x0, 0x0c0c0400u + b * 0x101u);
+  const uint32_t hi = __builtin_amdgcn_perm((uint32_t)x3, (uint32_t)x2, 0x04000c0cu + b * 0x1010000u);
+  return (int)(lo | hi);
 }
+// 4 int32 in [-128, 127] <-> 4 bytes (value v in byte v)
+__device__ __forceinline__ int pack4(i32x4 x) { return gather_bytes<0>(x[0], x[1], x[2], x[3]); }
 __device__ __forceinline__ i32x4 unpack4(int w) {
   i32x4 r;
 #pragma unroll
@@ -137,15 +144,21 @@ __device__ __forceinline__ int wave_max(int x) {
 // is zero by the structure of the computation), wave-wide
 template <int NB>
 __device__ __forceinline__ int amax_of(const AccI<NB>& D, int lo, int hi) {
-  int m = 0;
+  // the largest and the smallest value: one three-way maximum or minimum
+  // takes two values, an absolute value would cost an operation each
+  int mx = 0, mn = 0;
 #pragma unroll
   for (int I = 0; I < NB; ++I)
 #pragma unroll
     for (int J = 0; J <= I; ++J)
       if (blk_nz(I - J, lo, hi))
 #pragma unroll
-        for (int v = 0; v < 4; ++v) m = max(m, abs(D.a[bidx(I, J)][v]));
-  return wave_max(m);
+        for (int v = 0; v < 4; v += 2) {
+          const int a = D.a[bidx(I, J)][v], b = D.a[bidx(I, J)][v + 1];
+          mx = max(max(mx, a), b);
+          mn = min(min(mn, a), b);
+        }
+  return wave_max(max(mx, -mn));
 }
 
 
@@ -237,9 +250,8 @@ __device__ __forceinline__ int rne_scaled(double x, double sc) {
   return __double2loint(__builtin_fma(x, sc, kRoundMagic));
 }
 
-template <int NB> struct AccD { f64x4 a[nlower(NB)]; };  // fp64 integers
-
 __device__ __forceinline__ double elem(const i32x4& x, int v) { return (double)x[v]; }
+__device__ __forceinline__ double elem(const f32x4& x, int v) { return (double)x[v]; }
 __device__ __forceinline__ double elem(const f64x4& x, int v) { return x[v]; }
 
 // A term of an exact sum: the lower blocks of t (band [lo, hi]) times
@@ -260,9 +272,11 @@ __device__ __forceinline__ int term_bits(const Term<T>& x) {
   for (int I = 0; I < NB; ++I)
 #pragma unroll
     for (int J = 0; J <= I; ++J)
-      if (blk_nz(I - J, x.lo, x.hi))
+      if (blk_nz(I - J, x.lo, x.hi)) {
+        const auto q = x.t->a[bidx(I, J)];
 #pragma unroll
-        for (int v = 0; v < 4; ++v) mh = max(mh, __double2hiint(fabs(elem(x.t->a[bidx(I, J)], v))));
+        for (int v = 0; v < 4; ++v) mh = max(mh, __double2hiint(fabs(elem(q, v))));
+      }
   mh = wave_max(mh);
   if (mh == 0) return 0;
   int p;
@@ -332,8 +346,8 @@ __device__ __forceinline__ SumPlan sum_plan(const int (&e)[3], const int (&b)[3]
 // that a zero or small term does not widen the window (sum_plan).  Returns
 // the codes, their exponent and a non-zero flag; every block of out
 // outside the band is set to 0.
-template <int Q, int QB, int NB, typename T1, typename T2, typename T3>
-__device__ __forceinline__ void exact_sum(AccI<NB>& out, int& eo, bool& nz, const Term<T1>& x,
+template <int Q, int QB, int NB, typename TO, typename T1, typename T2, typename T3>
+__device__ __forceinline__ void exact_sum(TO& out, int& eo, bool& nz, const Term<T1>& x,
                                           const Term<T2>& y, const Term<T3>& z, int lo, int hi) {
   int e[3] = {x.e, y.e, z.e}, b[3] = {x.bits, y.bits, z.bits};
   bool p[3] = {x.p, y.p, z.p};
@@ -346,7 +360,7 @@ __device__ __forceinline__ void exact_sum(AccI<NB>& out, int& eo, bool& nz, cons
     }
   if (!p[0] && !p[1] && !p[2]) {
 #pragma unroll
-    for (int bb = 0; bb < nlower(NB); ++bb) out.a[bb] = zero_i4();
+    for (int bb = 0; bb < nlower(NB); ++bb) out.a[bb] = {};
     eo = 0;
     nz = false;
     return;
@@ -360,21 +374,23 @@ __device__ __forceinline__ void exact_sum(AccI<NB>& out, int& eo, bool& nz, cons
   const double sx = pl.p[0] ? (double)x.sign * ldexp(1.0, x.e - pl.emin) : 0.0;
   const double sy = pl.p[1] ? (double)y.sign * ldexp(1.0, y.e - pl.emin) : 0.0;
   const double sz = pl.p[2] ? (double)z.sign * ldexp(1.0, z.e - pl.emin) : 0.0;
-  auto val = [&](int I, int J, int v) {
+  // block (I, J) of the sum
+  auto val = [&](int I, int J) {
     const int m = I - J, bi = bidx(I, J);
-    double acc = 0.0;
-    if (pl.p[0] && blk_nz(m, x.lo, x.hi)) {
-      const double t = elem(x.t->a[bi], v) * sx;
-      acc += pl.r[0] ? rint(t) : t;
-    }
-    if (pl.p[1] && blk_nz(m, y.lo, y.hi)) {
-      const double t = elem(y.t->a[bi], v) * sy;
-      acc += pl.r[1] ? rint(t) : t;
-    }
-    if (pl.p[2] && blk_nz(m, z.lo, z.hi)) {
-      const double t = elem(z.t->a[bi], v) * sz;
-      acc += pl.r[2] ? rint(t) : t;
-    }
+    f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+    auto put = [&](const auto& t, bool p, bool r, double sc) {
+      if (p && blk_nz(m, t.lo, t.hi)) {
+        const auto q = t.t->a[bi];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const double d = elem(q, v) * sc;
+          acc[v] += r ? rint(d) : d;
+        }
+      }
+    };
+    put(x, pl.p[0], pl.r[0], sx);
+    put(y, pl.p[1], pl.r[1], sy);
+    put(z, pl.p[2], pl.r[2], sz);
     return acc;
   };
   int mh = 0;
@@ -382,9 +398,11 @@ __device__ __forceinline__ void exact_sum(AccI<NB>& out, int& eo, bool& nz, cons
   for (int I = 0; I < NB; ++I)
 #pragma unroll
     for (int J = 0; J <= I; ++J)
-      if (blk_nz(I - J, lo, hi))
+      if (blk_nz(I - J, lo, hi)) {
+        const f64x4 q = val(I, J);
 #pragma unroll
-        for (int v = 0; v < 4; ++v) mh = max(mh, __double2hiint(fabs(val(I, J, v))));
+        for (int v = 0; v < 4; ++v) mh = max(mh, __double2hiint(fabs(q[v])));
+      }
   const int amax_hi = wave_max(mh);
   nz = amax_hi > 0;
   const int s = nz ? shift_canon_hi<Q, QB>(amax_hi) : 0;
@@ -393,11 +411,12 @@ __device__ __forceinline__ void exact_sum(AccI<NB>& out, int& eo, bool& nz, cons
   for (int I = 0; I < NB; ++I)
 #pragma unroll
     for (int J = 0; J <= I; ++J) {
-      i32x4 r = zero_i4();
-      if (nz && blk_nz(I - J, lo, hi))
+      out.a[bidx(I, J)] = {};
+      if (nz && blk_nz(I - J, lo, hi)) {
+        const f64x4 q = val(I, J);
 #pragma unroll
-        for (int v = 0; v < 4; ++v) r[v] = rne_scaled(val(I, J, v), sc);
-      out.a[bidx(I, J)] = r;
+        for (int v = 0; v < 4; ++v) out.a[bidx(I, J)][v] = rne_scaled(q[v], sc);
+      }
     }
   eo = nz ? pl.emin + s : 0;
 }
@@ -409,46 +428,61 @@ __device__ __forceinline__ Term<T> term(const T& t, int e, int bits, int sign, i
 }
 template <typename T>
 __device__ __forceinline__ Term<T> no_term(const T& t) {
-  return Term<T>{&t, 0, 0, 1, 0, 0, false};
+  return Term<T>{&t, 0, 0, 1, 1 << 20, -(1 << 20), false};  // meets no block
+}
+
+// The sum of x over the 16 lanes of one g (rotations within rows of 16 lanes).
+__device__ __forceinline__ float row_sum(float x) {
+  auto ror = [](float y, auto n) {
+    return __builtin_bit_cast(
+        float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, y), 0x120 + decltype(n)::value, 0xf,
+                                        0xf, true));
+  };
+  x += ror(x, std::integral_constant<int, 8>{});
+  x += ror(x, std::integral_constant<int, 4>{});
+  x += ror(x, std::integral_constant<int, 2>{});
+  x += ror(x, std::integral_constant<int, 1>{});
+  return x;
+}
+
+// wave-wide maximum of non-negative floats, as a scalar
+__device__ __forceinline__ float wave_maxf(float x) {
+  return __builtin_bit_cast(
+      float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, __ockl_wfred_max_f32(x))));
 }
 
 // Is every column sum of |E| (codes of a lower matrix in row form, band
 // [lo, C-1], exponent e) at most 1?  Then |(P E)_ij| <= max|P| for any P,
 // so each residual power is bounded by the one before it.  Lane (g, c) of
 // a row-form block holds row c, columns 4g + v: the sum over a block's rows
-// runs over the 16 lanes of one g (xor-shuffles 1, 2, 4, 8), the sum over
-// block rows in the lane.
-template <int NB>
-__device__ __forceinline__ bool colsum_at_most_one(const AccI<NB>& E, int e, int lo) {
-  int best = 0;
+// runs over the 16 lanes of one g, the sum over block rows in the lane.
+// Sums of at most 64 codes below 2^15 are exact in fp32.
+template <int NB, typename V>
+__device__ __forceinline__ bool colsum_at_most_one(const V* E, int e, int lo) {
+  float best = 0.f;
 #pragma unroll
   for (int J = 0; J < NB; ++J)
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-      int sacc = 0;
+      float sacc = 0.f;
 #pragma unroll
       for (int I = J; I < NB; ++I)
-        if (blk_nz(I - J, lo, 16 * NB - 1)) sacc += abs(E.a[bidx(I, J)][v]);
-#pragma unroll
-      for (int d = 1; d < 16; d <<= 1) sacc += __shfl_xor(sacc, d);
-      best = max(best, sacc);
+        if (blk_nz(I - J, lo, 16 * NB - 1)) sacc += fabsf((float)E[bidx(I, J)][v]);
+      best = fmaxf(best, row_sum(sacc));
     }
-  const int m = wave_max(best);
-  if (m == 0) return true;
-  if (e >= 0) return m <= 1 && e == 0;
-  return -e >= 30 || m <= (1 << -e);
+  return ldexpf(wave_maxf(best), e) <= 1.f;  // (underflow: at most 1)
 }
 
 // identity codes (1 on the diagonal, exponent 0)
-template <int NB>
-__device__ __forceinline__ void eye_codes(AccI<NB>& D) {
+template <int NB, typename V>
+__device__ __forceinline__ void eye_codes(V* a) {
   const int g = lane_g(), c = lane_c();
 #pragma unroll
   for (int I = 0; I < NB; ++I)
 #pragma unroll
     for (int J = 0; J <= I; ++J)
 #pragma unroll
-      for (int v = 0; v < 4; ++v) D.a[bidx(I, J)][v] = (I == J && c == 4 * g + v) ? 1 : 0;
+      for (int v = 0; v < 4; ++v) a[bidx(I, J)][v] = (I == J && c == 4 * g + v) ? 1 : 0;
 }
 
 // ---------------------------------------------------------------------------
@@ -470,24 +504,25 @@ __device__ __forceinline__ void eye_codes(AccI<NB>& D) {
 // T_hat's tensor as codes Tr (row form) and its exponent eTo.  NC, SC >= 0
 // fix N and S at compile time; -1 takes them from Nrt, Srt.
 //
-// Ops<NB> supplies one code width: fragment types Row, Col (operands in row
-// and column form) and Prod (an exact product); kQ, kQB (the code range and
-// its bits), kAccB (log2 bound of a product's magnitude); to_row, to_col
-// (codes to fragments), codes (fragments back to codes), mm<OUTQ> (exact
-// product, blocks outside a band zero), requant (a product to codes by the
-// scale rule), canon (codes to the
-// finest scale that holds them), add (q of the sum of two tensors of codes,
-// the first known to be at its finest scale or not),
-// row_to_col (column-form fragments of a row-form one, through the
-// identity).  Every helper visits only the blocks that can meet the band of
-// sub-diagonals it is given; the other blocks are zero by the structure of
-// the computation.
+// Ops<NB> supplies one code width: Codes (a matrix of codes, lower blocks
+// a[bidx(I, J)], held as int32 or as integer-valued fp32), fragment types Row,
+// Col (operands in row and column form); kQ, kQB (the code range and its bits);
+// any (a code is non-zero), to_row, to_col (codes to fragments), codes
+// (fragments back to codes), mulq (q of the exact product of two fragments, as
+// codes and as row fragments), canon (codes to the finest scale that holds
+// them), add (q of the sum of two tensors of codes, the first known to be at
+// its finest scale or not), mul_sum (q of the exact sum of two tensors of codes
+// and a product), row_to_col (column-form fragments of a row-form one, through
+// the identity).  Every helper visits only the blocks
+// that can meet the band of sub-diagonals it is given; the other blocks are
+// zero by the structure of the computation.
 template <template <int> class Ops, int NB, bool PLAIN, int NC = -1, int SC = -1>
-__device__ __forceinline__ void int_engine(const AccI<NB>& Lr, int eL, int Nrt, int Srt,
-                                           AccI<NB>& Tr, int& eTo) {
+__device__ __forceinline__ void int_engine(const typename Ops<NB>::Codes& Lr, int eL, int Nrt,
+                                           int Srt, typename Ops<NB>::Codes& Tr, int& eTo) {
   using O = Ops<NB>;
+  using Codes = typename O::Codes;
   constexpr int C = 16 * NB;
-  constexpr int Q = O::kQ, QB = O::kQB, ACCB = O::kAccB;
+  constexpr int QB = O::kQB;
   constexpr int U0 = PLAIN ? 0 : 1;  // lowest sub-diagonal of T0's, T's and T_hat's tensors
   const int N = NC >= 0 ? NC : Nrt;
   const int S = SC >= 0 ? SC : Srt;
@@ -495,33 +530,31 @@ __device__ __forceinline__ void int_engine(const AccI<NB>& Lr, int eL, int Nrt, 
   ColQ<NB> Ic;
   eye_quads(Iq, Ic);
 
-  const bool nzL = amax_of(Lr, 1, C - 1) > 0;
+  const bool nzL = O::any(Lr, 1, C - 1);
   typename O::Row LRq;
   O::to_row(LRq, Lr, 1, C - 1);
   typename O::Col LCq;
   O::row_to_col(LCq, LRq, Ic, 1, C - 1);
 
   // ---- T0 = sum_{n=0}^{N} L^n, then masked
-  AccI<NB> T0;
+  Codes T0;
   int eT0 = 0;
   bool nzT0 = PLAIN;
-  if constexpr (PLAIN) eye_codes(T0);
+  if constexpr (PLAIN) eye_codes<NB>(T0.a);
   else {
 #pragma unroll
-    for (int b = 0; b < nlower(NB); ++b) T0.a[b] = zero_i4();
+    for (int b = 0; b < nlower(NB); ++b) T0.a[b] = {};
   }
   if (N >= 1) {
-    AccI<NB> P = Lr;
+    Codes P = Lr;
     int eP = eL;
     bool nzP = nzL;
     O::canon(P, 1, C - 1, eP, nzP);
     O::add(T0, eT0, nzT0, U0, !PLAIN, P, eP, nzP, 1, 1, U0, C - 1);
     typename O::Row PRq;
+    O::to_row(PRq, P, 1, C - 1);
     auto power = [&](int n) {
-      O::to_row(PRq, P, n - 1, C - 1);
-      typename O::Prod D;
-      O::template mm<true>(D, PRq, LCq, n, C - 1);
-      O::requant(D, P, n, C - 1, eP + eL, eP, nzP);
+      O::mulq(PRq, LCq, n, C - 1, eP + eL, P, PRq, eP, nzP);
       O::add(T0, eT0, nzT0, U0, true, P, eP, nzP, 1, n, U0, C - 1);
     };
     if constexpr (NC >= 0) {
@@ -531,8 +564,8 @@ __device__ __forceinline__ void int_engine(const AccI<NB>& Lr, int eL, int Nrt, 
       for (int n = 2; n <= N; ++n) power(n);
     }
   }
-  band_i<NB, false>(T0, U0, N);
-  nzT0 = amax_of(T0, U0, N) > 0;
+  band_blocks<NB, false>(T0.a, U0, N);
+  nzT0 = O::any(T0, U0, N);
   typename O::Row T0Rq;
   O::to_row(T0Rq, T0, U0, N);
   typename O::Col T0Cq;
@@ -540,28 +573,23 @@ __device__ __forceinline__ void int_engine(const AccI<NB>& Lr, int eL, int Nrt, 
 
   // ---- E = I - q((I + A) T0), with (I + A) T0 = T0 - Lm T0
   constexpr int E0 = PLAIN ? 0 : 1;  // lowest sub-diagonal of E
-  AccI<NB> E;
+  Codes E;
   int eE;
   bool nzE;
-  {
-    typename O::Prod D;
-    O::template mm<true>(D, LRq, T0Cq, U0 + 1, C - 1);  // Lm T0
-    if constexpr (!PLAIN) {
-      // E = -(A + N0 + A N0) = Lm - N0 + Lm N0
-      exact_sum<Q, QB, NB>(E, eE, nzE, term(Lr, eL, QB, 1, 1, C - 1, nzL),
-                           term(T0, eT0, QB, -1, 1, N, nzT0),
-                           term(D, eL + eT0, ACCB, 1, 2, C - 1, nzL && nzT0), 1, C - 1);
-    } else {
-      AccI<NB> M;
-      int eM;
-      bool nzM;
-      exact_sum<Q, QB, NB>(M, eM, nzM, term(T0, eT0, QB, 1, 0, N, nzT0), no_term(T0),
-                           term(D, eL + eT0, ACCB, -1, 1, C - 1, nzL && nzT0), 0, C - 1);
-      eye_codes(E);
-      eE = 0;
-      nzE = true;
-      O::add(E, eE, nzE, 0, false, M, eM, nzM, -1, 0, 0, C - 1);
-    }
+  if constexpr (!PLAIN) {
+    // E = -(A + N0 + A N0) = Lm - N0 + Lm N0
+    O::mul_sum(E, eE, nzE, term(Lr, eL, QB, 1, 1, C - 1, nzL), term(T0, eT0, QB, -1, 1, N, nzT0),
+               LRq, T0Cq, eL + eT0, 1, 2, nzL && nzT0, 1, C - 1);
+  } else {
+    Codes M;
+    int eM;
+    bool nzM;
+    O::mul_sum(M, eM, nzM, term(T0, eT0, QB, 1, 0, N, nzT0), no_term(T0), LRq, T0Cq, eL + eT0, -1,
+               1, nzL && nzT0, 0, C - 1);
+    eye_codes<NB>(E.a);
+    eE = 0;
+    nzE = true;
+    O::add(E, eE, nzE, 0, false, M, eM, nzM, -1, 0, 0, C - 1);
   }
   typename O::Row ERq;
   O::to_row(ERq, E, E0, C - 1);
@@ -569,17 +597,16 @@ __device__ __forceinline__ void int_engine(const AccI<NB>& Lr, int eL, int Nrt, 
   O::row_to_col(ECq, ERq, Ic, E0, C - 1);
 
   // ---- T = sum_{s=0}^{S} E^s
-  AccI<NB> R;
+  Codes R;
   int eR = 0;
   bool nzR = PLAIN;
-  if constexpr (PLAIN) eye_codes(R);
+  if constexpr (PLAIN) eye_codes<NB>(R.a);
   else {
 #pragma unroll
-    for (int b = 0; b < nlower(NB); ++b) R.a[b] = zero_i4();
+    for (int b = 0; b < nlower(NB); ++b) R.a[b] = {};
   }
   if (S >= 1) {
     O::add(R, eR, nzR, U0, !PLAIN, E, eE, nzE, 1, E0, U0, C - 1);
-    AccI<NB> P;
     int eP = eE;
     bool nzP = nzE;
     typename O::Row PRq = ERq;
@@ -588,25 +615,17 @@ __device__ __forceinline__ void int_engine(const AccI<NB>& Lr, int eL, int Nrt, 
     // column sum of |E| is at most 1, every later power is no larger, its
     // exponent no higher, and its add leaves T as it is too: the chain
     // stops there with the result it would have reached.
-    const bool contracting = colsum_at_most_one(E, eE, E0);
-    bool done = false;
-    auto chain = [&](int s) {
-      if (done) return;
-      const int lo = PLAIN ? 0 : s;
-      typename O::Prod D;
-      O::template mm<true>(D, PRq, ECq, lo, C - 1);
-      O::requant(D, P, lo, C - 1, eP + eE, eP, nzP);
-      const bool idle = !nzP || (nzR && eR - eP >= 2 * QB + 3);
-      O::add(R, eR, nzR, U0, true, P, eP, nzP, 1, lo, U0, C - 1);
-      done = idle && contracting;
-      if (!done) O::to_row(PRq, P, lo, C - 1);
-    };
+    const bool contracting = colsum_at_most_one<NB>(E.a, eE, E0);
     // a rolled loop: unrolled, the early exit keeps every iteration's
     // operands live at once and costs a wave per SIMD
 #pragma unroll 1
     for (int s = 2; s <= S; ++s) {
-      chain(s);
-      if (done) break;
+      const int lo = PLAIN ? 0 : s;
+      Codes P;
+      O::mulq(PRq, ECq, lo, C - 1, eP + eE, P, PRq, eP, nzP);
+      const bool idle = !nzP || (nzR && eR - eP >= 2 * QB + 3);
+      O::add(R, eR, nzR, U0, true, P, eP, nzP, 1, lo, U0, C - 1);
+      if (idle && contracting) break;
     }
   }
 
@@ -617,21 +636,35 @@ __device__ __forceinline__ void int_engine(const AccI<NB>& Lr, int eL, int Nrt, 
     O::to_row(RRq, R, U0, C - 1);
     O::row_to_col(RCq, RRq, Ic, U0, C - 1);
   }
-  typename O::Prod D;
-  O::template mm<true>(D, T0Rq, RCq, PLAIN ? 0 : 2, C - 1);
-  // T0's codes again, from its row fragments (they hold every code exactly;
-  // keeping the unpacked copy alive across the residual chain would cost a
-  // wave per SIMD)
-  O::codes(T0, T0Rq, U0, N);
+  bool nzT;
   if constexpr (!PLAIN) {
-    bool nzT;
-    exact_sum<Q, QB, NB>(Tr, eTo, nzT, term(T0, eT0, QB, 1, 1, N, nzT0),
-                         term(R, eR, QB, 1, 1, C - 1, nzR),
-                         term(D, eT0 + eR, ACCB, 1, 2, C - 1, nzT0 && nzR), 1, C - 1);
+    // T0's codes again, from its row fragments (they hold every code exactly;
+    // keeping the unpacked copy alive across the residual chain would cost a
+    // wave per SIMD)
+    O::codes(T0, T0Rq, U0, N);
+    O::mul_sum(Tr, eTo, nzT, term(T0, eT0, QB, 1, 1, N, nzT0), term(R, eR, QB, 1, 1, C - 1, nzR),
+               T0Rq, RCq, eT0 + eR, 1, 2, nzT0 && nzR, 1, C - 1);
   } else {
-    bool nzT;
-    O::requant(D, Tr, 0, C - 1, eT0 + eR, eTo, nzT);
+    typename O::Row unused;
+    O::mulq(T0Rq, RCq, 0, C - 1, eT0 + eR, Tr, unused, eTo, nzT);
   }
+}
+
+// The same on int32 codes in and out, whatever the width holds codes in.
+template <template <int> class Ops, int NB, bool PLAIN, int NC = -1, int SC = -1>
+__device__ __forceinline__ void int_engine_i32(const AccI<NB>& Lr, int eL, int Nrt, int Srt,
+                                               AccI<NB>& Tr, int& eTo) {
+  typename Ops<NB>::Codes L, T;
+  using E = std::remove_reference_t<decltype(L.a[0][0] + L.a[0][0])>;
+#pragma unroll
+  for (int b = 0; b < nlower(NB); ++b)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) L.a[b][v] = (E)Lr.a[b][v];
+  int_engine<Ops, NB, PLAIN, NC, SC>(L, eL, Nrt, Srt, T, eTo);
+#pragma unroll
+  for (int b = 0; b < nlower(NB); ++b)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) Tr.a[b][v] = (int)T.a[b][v];
 }
 
 }  // namespace iq

@@ -475,8 +475,9 @@ def bench_forward(a, w, C, N, S, default_order, G, torch):
     fws_ms, _ = _kernel_time(lambda: G.gdn_chunk_inverse_fwdsub(dA, Tinv=dT), dT,
                              max(1, a.steps // 4), stream, torch)
     del dA, dT
-    # algorithmic bytes per launch
-    # workspace: W, U, K^T and the masked Q K^T per chunk, written once, read once
+    # algorithmic bytes per launch of the two launches as separate calls (the
+    # ones timed here): the workspace holds G, P' and copies of K and V per
+    # chunk, written once, read once
     ws_b = G.gdn_chunk_forward_workspace(w.B, w.L, w.H, w.dk, w.dv, C, dt)
     prep_bytes = tok * (2 * w.dk + w.dv) * es + tok * 8 + ws_b
     state_bytes = ws_b + tok * (w.dk + w.dv) * es + tok * 4 + 2 * w.B * w.H * w.dk * w.dv * 4
@@ -567,8 +568,12 @@ def bench_forward_varlen(a, w, C, N, S, G, torch):
     ms_per_step = wall * 1e3 / a.steps
     tok = T * w.H
     ws_b = G.gdn_chunk_forward_workspace(1, n_chunks * C, w.H, w.dk, w.dv, C, dt)
-    layer_bytes = (tok * (2 * w.dk + w.dv) * es + tok * 8 + 2 * ws_b + tok * (w.dk + w.dv) * es
-                   + tok * 4 + 2 * len(lengths) * w.H * w.dk * w.dv * 4)
+    # one call: the per-chunk launch reads Q and K, the state pass Q, K and V;
+    # G, P' and the chunk's gates pass between them (the workspace's copies of K
+    # and V are for the two launches as separate calls)
+    fac_b = ws_b - n_tiles * C * (w.dk + w.dv) * es + n_tiles * C * 4
+    layer_bytes = (tok * 2 * w.dk * es + tok * 8 + 2 * fac_b + tok * 2 * (w.dk + w.dv) * es
+                   + 2 * len(lengths) * w.H * w.dk * w.dv * 4)
     achieved = layer_bytes / (ev_ms * 1e-3) / 1e9
     out = {
         "metric": METRIC,
@@ -773,7 +778,7 @@ PROFILES = {("fused", "qwen35_prefill", 64): ("k_fused_qwen35_prefill.md", "pipe
             ("int16", "int8", 64): ("k_inverse_i16_fused_int8.md", "int16.hip"),
             ("int8", "int8", 128): ("k_inverse_int128_fused_i8_int8.md", "int8.hip"),
             ("int16", "int8", 128): ("k_inverse_int128_fused_i16_int8.md", "int16.hip"),
-            ("forward", "qwen35_prefill", 64): ("k_fwd_state_qwen35_prefill.md", "forward.hip")}
+            ("forward", "qwen35_prefill", 64): ("k_fwd_state_qwen35_prefill.md", "state.hip")}
 
 
 def measured_traffic(path, workload, C, N, S, default_order):

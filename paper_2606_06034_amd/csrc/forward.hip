@@ -29,55 +29,56 @@ int64_t fwd_workspace_elems(int C, int dk, int dv) {
          (int64_t)(dk / 16) * np * 512 + (int64_t)npp(NB) * 512;
 }
 
-// Column-form blocks of a 32-feature run of X (rows of the chunk), made by
-// identity MFMAs: y[h][p] pairs t-blocks {2p, 2p + 1}; column n of half h is
-// feature 32q + 8 (n / 4) + 4h + n % 4.
-template <int NB, typename F>
-__device__ __forceinline__ void run_to_cols(Pair<F> (&y)[2][npair(NB)], const Pair<F> (&x)[NB],
-                                            Lane ln) {
+// Column-form block of a 32-feature run of X (16 rows of the chunk), made by
+// an identity MFMA (exact): column n of half h is feature
+// 32q + 8 (n / 4) + 4h + n % 4.
+template <typename F>
+__device__ __forceinline__ f32x4 run_to_col(const Pair<F>& x, int h, Lane ln) {
   const f32x4 e = eye4(ln);
-  const Pair<F> id0 = Pair<F>::make(e, zero4()), id1 = Pair<F>::make(zero4(), e);
-#pragma unroll
-  for (int h = 0; h < 2; ++h)
-#pragma unroll
-    for (int p = 0; p < npair(NB); ++p) {
-      const f32x4 a = Pair<F>::template mma<false>(x[2 * p], h ? id1 : id0, zero4());
-      const f32x4 b = (2 * p + 1 < NB)
-                          ? Pair<F>::template mma<false>(x[2 * p + 1], h ? id1 : id0, zero4())
-                          : zero4();
-      y[h][p] = Pair<F>::make(a, b);
-    }
+  return Pair<F>::template mma<false>(x, h ? Pair<F>::make(zero4(), e) : Pair<F>::make(e, zero4()),
+                                      zero4());
 }
 
-// G = K^T T~ (T~ = diag(e^{gamma_last - gamma}) T diag(beta) as column pairs)
-// as row pairs per state block, from the column-form blocks of K (= row pairs
-// of K^T).
+// G = K^T diag(d) T diag(beta), d = e^{gamma_last - gamma}, as row pairs per
+// state block, from the column-form blocks of K (= row pairs of K^T) and NC,
+// the column pairs of diag(d) (T - I) diag(beta): the unit diagonal of T
+// contributes K^T diag(db), db = d beta, through the accumulator, which no
+// operand rounding touches.  (As an operand in 16 bits, beta on the diagonal
+// would be off by the same factor in every row where beta is constant, an
+// error that adds up over keys that share a direction.)  fp32 adds that term
+// last: the partial sums, and so their roundings, stay small.
 template <int NB, int DK, typename F, typename TIO>
-__device__ __forceinline__ void apply_g(const ColP<NB, F>& TC, const Pair<F> (&kp)[NB][DK / 32],
-                                        TIO* __restrict__ gf, Lane ln) {
+__device__ __forceinline__ void apply_g(const ColP<NB, F>& NC, const Pair<F> (&kp)[NB][DK / 32],
+                                        const float* sdb, TIO* __restrict__ gf, Lane ln) {
   constexpr int NP = npair(NB);
+  constexpr bool LAST = sizeof(TIO) == 4;
 #pragma unroll
   for (int q = 0; q < DK / 32; ++q) {
-    Pair<F> x[NB];
-#pragma unroll
-    for (int I = 0; I < NB; ++I) x[I] = kp[I][q];
     Pair<F> y[2][NP];
-    run_to_cols<NB, F>(y, x, ln);
+    f32x4 acc[2][2 * NP];
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      f32x4 acc[2 * NP];
 #pragma unroll
-      for (int J = 0; J < 2 * NP; ++J) {
-        acc[J] = zero4();
-        if (J < NB)
+      for (int J = 0; J < 2 * NP; ++J)
+        acc[h][J] = J < NB ? run_to_col<F>(kp[J < NB ? J : 0][q], h, ln) : zero4();
 #pragma unroll
-          for (int p = J / 2; p < NP; ++p)
-            acc[J] = Pair<F>::template mma<true>(y[h][p], TC.c[p][J], acc[J]);
+      for (int p = 0; p < NP; ++p) y[h][p] = Pair<F>::make(acc[h][2 * p], acc[h][2 * p + 1]);
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+#pragma unroll
+      for (int J = 0; J < NB; ++J) {
+        const f32x4 kd = acc[h][J] * *(const f32x4*)(sdb + 16 * J + 4 * ln.g());
+        acc[h][J] = LAST ? zero4() : kd;
+#pragma unroll
+        for (int p = J / 2; p < NP; ++p)
+          acc[h][J] = Pair<F>::template mma<true>(y[h][p], NC.c[p][J], acc[h][J]);
+        if (LAST) acc[h][J] += kd;
       }
 #pragma unroll
       for (int p = 0; p < NP; ++p)
-        slot_store(gf + ((2 * q + h) * NP + p) * 512, Pair<F>::make(acc[2 * p], acc[2 * p + 1]),
-                   ln.id);
+        slot_store(gf + ((2 * q + h) * NP + p) * 512,
+                   Pair<F>::make(acc[h][2 * p], acc[h][2 * p + 1]), ln.id);
     }
   }
 }
@@ -162,7 +163,7 @@ __global__ __launch_bounds__(64) void k_fwd_chunk(const TIO* __restrict__ Q,
   // bf16: Q arrives in LDS by DMA while registers are busy
   constexpr bool PREF = sizeof(TIO) == 2;
   using LY = FwdLayout<NB, DK, DV>;
-  __shared__ float sb[C], sg[C], sd[C];
+  __shared__ __attribute__((aligned(16))) float sb[C], sg[C], sd[C], sdb[C];
   __shared__ __attribute__((aligned(16))) __bf16 sx[PREF ? NB * (DK / 32) * 512 : 8];
   Chunk ch;
   if constexpr (VARLEN)
@@ -187,6 +188,7 @@ __global__ __launch_bounds__(64) void k_fwd_chunk(const TIO* __restrict__ Q,
   stash_gates<C>(gr, sb, sg);
   for (int r = ln.id; r < C; r += 64) {
     sd[r] = __expf(sg[C - 1] - sg[r]);
+    sdb[r] = sd[r] * sb[r];
     if (!split) ((float*)rest)[tile * C + r] = sg[r];
   }
   __syncthreads();
@@ -202,17 +204,16 @@ __global__ __launch_bounds__(64) void k_fwd_chunk(const TIO* __restrict__ Q,
     chunk_inverse_int<NB, DK, F, INV, NC, SC>(kp, sb, sg, N, S, Tr, prefetch_q);
   else
     chunk_inverse<NB, DK, F, SMALLN, NC, SC, INV == kInvExact>(kp, sb, sg, N, S, Tr, prefetch_q);
-  // T' = T diag(beta)
+  // (T - I) diag(beta)
 #pragma unroll
-  for (int I = 0; I < NB; ++I) Tr.a[bidx(I, I)] = band_block<false>(Tr.a[bidx(I, I)], 0, 1, C) + eye4();
+  for (int I = 0; I < NB; ++I) Tr.a[bidx(I, I)] = band_block<false>(Tr.a[bidx(I, I)], 0, 1, C);
 #pragma unroll
   for (int I = 0; I < NB; ++I)
 #pragma unroll
-    for (int J = 0; J <= I; ++J)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) Tr.a[bidx(I, J)][v] *= sb[16 * J + 4 * ln.g() + v];
+    for (int J = 0; J <= I; ++J) Tr.a[bidx(I, J)] *= *(const f32x4*)(sb + 16 * J + 4 * ln.g());
 
-  // P = (Q K^T) (.) D, lower blocks in row form, and P' = P T'
+  // P = (Q K^T) (.) D, lower blocks in row form, and P' = P T diag(beta) = P
+  // diag(beta) + P (T - I) diag(beta), the first term not rounded (as in apply_g)
   {
     Acc<NB> Pm;
 #pragma unroll
@@ -249,7 +250,18 @@ __global__ __launch_bounds__(64) void k_fwd_chunk(const TIO* __restrict__ Q,
     to_rowp(PR, Pm);
     ColP<NB, F> TC;
     rows_to_colp(TC, Tr, ln);
-    mm<NB, true, false>(Pm, PR, 0, C - 1, TC, 0, C - 1, 0, C - 1);
+#pragma unroll
+    for (int I = 0; I < NB; ++I)
+#pragma unroll
+      for (int J = 0; J <= I; ++J) Pm.a[bidx(I, J)] *= *(const f32x4*)(sb + 16 * J + 4 * ln.g());
+    if constexpr (sizeof(TIO) == 2) {
+      mm<NB, true, true>(Pm, PR, 0, C - 1, TC, 1, C - 1, 0, C - 1);
+    } else {
+      Acc<NB> D;
+      mm<NB, true, false>(D, PR, 0, C - 1, TC, 1, C - 1, 0, C - 1);
+#pragma unroll
+      for (int b = 0; b < nlower(NB); ++b) Pm.a[b] += D.a[b];
+    }
 #pragma unroll
     for (int I = 0; I < NB; ++I)
 #pragma unroll
@@ -258,14 +270,14 @@ __global__ __launch_bounds__(64) void k_fwd_chunk(const TIO* __restrict__ Q,
                    ln.id);
   }
 
-  // G = K^T diag(e^{gamma_last - gamma}) T' (row i of T' is row c of its block)
+  // G (row i of T is row c of its block)
 #pragma unroll
   for (int I = 0; I < NB; ++I)
 #pragma unroll
     for (int J = 0; J <= I; ++J) Tr.a[bidx(I, J)] *= sd[16 * I + ln.c()];
   ColP<NB, F> TC;
   rows_to_colp(TC, Tr, ln);
-  apply_g<NB, DK, F>(TC, kp, gf, ln);
+  apply_g<NB, DK, F>(TC, kp, sdb, gf, ln);
 
   if (!VARLEN && split) {
     TIO* kc = rest + tile * LY::KC;

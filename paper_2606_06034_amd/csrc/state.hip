@@ -157,6 +157,7 @@ __global__ __launch_bounds__((64 * StateShape<NB, DK, TIO, NSL, RS, R>::WAVES)) 
   using KR = typename SH::KR;
   constexpr int C = SH::C, NQ = SH::NQ, NP = SH::NP, NS = DV / (16 * NSL);
   constexpr int SW = SH::SWV, OW = SH::OW;
+  constexpr int PS = sizeof(TIO) == 4 ? 2 : 1;  // partial sums of a product with the state
   __shared__ __attribute__((aligned(16))) TIO sK[R][C * DK];
   __shared__ __attribute__((aligned(16))) TIO sQ[R][16 * OW * DK];
   __shared__ __attribute__((aligned(16))) TIO sV[R][SH::VN];
@@ -287,19 +288,23 @@ __global__ __launch_bounds__((64 * StateShape<NB, DK, TIO, NSL, RS, R>::WAVES)) 
         __builtin_amdgcn_sched_barrier(0);
         load_g(nx, cknx);
         __builtin_amdgcn_sched_barrier(0);
-        f32x4 ks[NSL];
+        // (fp32: two partial sums, whose roundings are smaller than one's)
+        f32x4 ks[NSL][PS];
 #pragma unroll
-        for (int s = 0; s < NSL; ++s) ks[s] = zero4();
+        for (int s = 0; s < NSL; ++s)
+#pragma unroll
+          for (int u = 0; u < PS; ++u) ks[s][u] = zero4();
 #pragma unroll
         for (int q = 0; q < NQ; ++q)
 #pragma unroll
           for (int s = 0; s < NSL; ++s)
-            ks[s] = Pair<F>::template mma<false>(kr[q], sp[s][q], ks[s]);
+            ks[s][q % PS] = Pair<F>::template mma<false>(kr[q], sp[s][q], ks[s][q % PS]);
 #pragma unroll
         for (int s = 0; s < NSL; ++s) {
+          if constexpr (PS == 2) ks[s][0] += ks[s][1];
           f32x4 xc;
 #pragma unroll
-          for (int v = 0; v < 4; ++v) xc[v] = vc[s][v] - eg[v] * ks[s][v];
+          for (int v = 0; v < 4; ++v) xc[v] = vc[s][v] - eg[v] * ks[s][0][v];
           slot_store_half(xv[s] + (I >> 1) * 512, xc, I & 1, l);
         }
       } else {
@@ -316,10 +321,16 @@ __global__ __launch_bounds__((64 * StateShape<NB, DK, TIO, NSL, RS, R>::WAVES)) 
       read_rows(bufnx);
       __builtin_amdgcn_sched_barrier(0);
       if (owner) {
+        // fp32: the decayed state is added last, so that only the last
+        // addition rounds at its size
+        f32x4 old[NSL][2];
 #pragma unroll
         for (int s = 0; s < NSL; ++s)
 #pragma unroll
-          for (int hf = 0; hf < 2; ++hf) st[s][hf] *= el;
+          for (int hf = 0; hf < 2; ++hf) {
+            old[s][hf] = st[s][hf];
+            st[s][hf] = PS == 2 ? zero4() : old[s][hf] * el;
+          }
 #pragma unroll
         for (int p = 0; p < NP; ++p)
 #pragma unroll
@@ -327,6 +338,14 @@ __global__ __launch_bounds__((64 * StateShape<NB, DK, TIO, NSL, RS, R>::WAVES)) 
 #pragma unroll
             for (int hf = 0; hf < 2; ++hf)
               st[s][hf] = Pair<F>::template mma<false>(op.x[hf][p], xp[s][p], st[s][hf]);
+        if constexpr (PS == 2)
+#pragma unroll
+          for (int s = 0; s < NSL; ++s)
+#pragma unroll
+            for (int hf = 0; hf < 2; ++hf)
+#pragma unroll
+              for (int v = 0; v < 4; ++v)
+                st[s][hf][v] = __builtin_fmaf(el, old[s][hf][v], st[s][hf][v]);
       }
       __builtin_amdgcn_sched_barrier(0);
     };

@@ -71,6 +71,28 @@ __device__ __forceinline__ void hold(Pair<f32x4>& x) {
   hold(x.b);
 }
 
+// Pairs over the chunk's rows and their products.  NB = 1: the second block of
+// the pair does not exist (zeros); in fp32 it is neither loaded nor multiplied.
+template <int NB, typename F, typename TIO>
+__device__ __forceinline__ Pair<F> rows_load(const TIO* s, int l) {
+  if constexpr (NB == 1 && sizeof(TIO) == 4)
+    return Pair<F>::make(*(const f32x4*)(s + 4 * l), zero4());
+  else
+    return slot_load<F>(s, l);
+}
+template <int NB, bool OUTQ, typename F>
+__device__ __forceinline__ f32x4 rows_mma(const Pair<F>& x, const Pair<F>& y, f32x4 acc) {
+  if constexpr (NB == 1 && std::is_same_v<F, f32x4>) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(OUTQ ? y.a[v] : x.a[v], OUTQ ? x.a[v] : y.a[v],
+                                                 acc, 0, 0, 0);
+    return acc;
+  } else {
+    return Pair<F>::template mma<OUTQ>(x, y, acc);
+  }
+}
+
 // NSL x 4 consecutive values of a row
 template <typename F, int NSL> struct Run { Pair<F> v; };
 template <typename F> struct Run<F, 1> { F v; };
@@ -115,14 +137,29 @@ template <int NB, int DK, typename TIO, int NSL, int RS, int R>
 struct StateShape {
   static constexpr int C = 16 * NB, NQ = DK / 32, NP = npair(NB);
   static constexpr int SWV = NB > NQ ? NB : NQ;  // recurrence waves
-  static constexpr int OW = NB / RS;             // output waves
   // loader waves: a wave issues a copy of strided rows every 27 ns, a CU takes
   // one every 10 ns (fp32: two, the registers of a third wave per SIMD are
   // worth more)
   static constexpr int LW = sizeof(TIO) == 2 ? 4 : 2;
+  // row blocks of O an output wave forms: one, but in fp32 two where more
+  // output waves would be the third wave on a SIMD (168 registers a lane: the
+  // 189 to 200 of C = 64 did not fit and went to scratch within the chain)
+  static constexpr int OB = sizeof(TIO) == 4 && SWV + NB / RS + LW > 8 ? 2 : 1;
+  static constexpr int OW = NB / RS / OB;  // output waves
   static constexpr int WAVES = SWV + OW + LW;
+  // The first output and loader wave.  Waves go to the four SIMDs in turn; where
+  // only the first of four recurrence waves have rows (NB < 4), the loaders come
+  // before the output waves, which then have SIMDs of their own (fp32, us of the
+  // layer at 2048 tokens, 4 heads: C = 32 119 -> 97, C = 16 186 -> 144).
+  static constexpr bool LFIRST = sizeof(TIO) == 4 && SWV == 4 && NB < 4;
+  static constexpr int O0 = SWV + (LFIRST ? LW : 0), L0 = SWV + (LFIRST ? 0 : OW);
+  // Workgroups a CU is to hold.  fp32, one slice each without sharing: two
+  // where their LDS fits, as the launch rule counts on (run_state).
+  static constexpr bool TWO =
+      sizeof(TIO) == 4 && NSL == 1 && RS == 1 && (NB == 1 || (NB == 4 && DK == 64 && R == 1));
+  static constexpr int PER_SIMD = (TWO ? 2 : 1) * ((WAVES + 3) / 4);  // waves
   using KR = SwzRows<DK, TIO>;
-  static constexpr int KI = C / KR::RPI, QI = 16 * OW / KR::RPI;  // copies a chunk
+  static constexpr int KI = C / KR::RPI, QI = 16 * OW * OB / KR::RPI;  // copies a chunk
   static constexpr int VL = NSL * 16 * (int)sizeof(TIO) / 16;     // lanes a row of V
   static constexpr int VR = 64 / VL;                              // rows of V a copy
   static constexpr int VI = (C + VR - 1) / VR;
@@ -145,9 +182,9 @@ struct StateShape {
 // of 8: work items are dealt to the 8 XCDs in turn and XCD k takes the heads
 // bh0 + k, bh0 + k + 8, ... whole, so the operands that a head's workgroups
 // all read meet in one L2.
-template <int NB, int DK, int DV, typename F, typename TIO, int NSL, int RS, int R, int GD,
-          bool VARLEN>
-__global__ __launch_bounds__((64 * StateShape<NB, DK, TIO, NSL, RS, R>::WAVES)) void k_fwd_state(
+template <int NB, int DK, int DV, typename F, typename TIO, int NSL, int RS, int R, bool VARLEN>
+__global__ __launch_bounds__((64 * StateShape<NB, DK, TIO, NSL, RS, R>::WAVES),
+                             (StateShape<NB, DK, TIO, NSL, RS, R>::PER_SIMD)) void k_fwd_state(
     const TIO* __restrict__ ws, const TIO* __restrict__ Q, const TIO* __restrict__ K,
     const TIO* __restrict__ V, const float* __restrict__ gam, int gtiles,
     const float* __restrict__ S0, TIO* __restrict__ O, float* __restrict__ Sfin, int64_t n_tiles,
@@ -156,10 +193,16 @@ __global__ __launch_bounds__((64 * StateShape<NB, DK, TIO, NSL, RS, R>::WAVES)) 
   using LY = FwdLayout<NB, DK, DV>;
   using KR = typename SH::KR;
   constexpr int C = SH::C, NQ = SH::NQ, NP = SH::NP, NS = DV / (16 * NSL);
-  constexpr int SW = SH::SWV, OW = SH::OW;
+  constexpr int SW = SH::SWV, OW = SH::OW, OB = SH::OB;
   constexpr int PS = sizeof(TIO) == 4 ? 2 : 1;  // partial sums of a product with the state
+  // Register sets of G and P': bf16 loads the next chunk's while it works on
+  // this one's.  fp32 loads its own at the state barrier, behind the product
+  // with the state, which takes longer than the load (us of the layer at 2048
+  // tokens, 16 heads, C = 64: 143 -> 136) but for the smallest (C = 32, dk = 64:
+  // 72 -> 74), and half the registers.
+  constexpr int GD = sizeof(TIO) == 4 && !(NB == 2 && DK == 64) ? 1 : 2;
   __shared__ __attribute__((aligned(16))) TIO sK[R][C * DK];
-  __shared__ __attribute__((aligned(16))) TIO sQ[R][16 * OW * DK];
+  __shared__ __attribute__((aligned(16))) TIO sQ[R][16 * OW * OB * DK];
   __shared__ __attribute__((aligned(16))) TIO sV[R][SH::VN];
   __shared__ __attribute__((aligned(16))) float sg[R][64];
   __shared__ __attribute__((aligned(16))) TIO xs[NSL][NQ * 512];  // state pairs
@@ -229,7 +272,8 @@ __global__ __launch_bounds__((64 * StateShape<NB, DK, TIO, NSL, RS, R>::WAVES)) 
         for (int hf = 0; hf < 2; ++hf)
 #pragma unroll
           for (int p = 0; p < NP; ++p)
-            op.x[hf][p] = slot_load<F>(wsG + ck * H * LY::G + ((2 * wv + hf) * NP + p) * 512, l);
+            op.x[hf][p] =
+                rows_load<NB, F>(wsG + ck * H * LY::G + ((2 * wv + hf) * NP + p) * 512, l);
     };
     // this chunk's K row pairs, V row and gammas, from LDS
     Pair<F> kr[NQ];
@@ -316,7 +360,7 @@ __global__ __launch_bounds__((64 * StateShape<NB, DK, TIO, NSL, RS, R>::WAVES)) 
 #pragma unroll
         for (int p = 0; p < NP; ++p)
 #pragma unroll
-          for (int s = 0; s < NSL; ++s) xp[s][p] = slot_load<F>(xv[s] + p * 512, l);
+          for (int s = 0; s < NSL; ++s) xp[s][p] = rows_load<NB, F>(xv[s] + p * 512, l);
       __builtin_amdgcn_sched_barrier(0);
       read_rows(bufnx);
       __builtin_amdgcn_sched_barrier(0);
@@ -337,7 +381,7 @@ __global__ __launch_bounds__((64 * StateShape<NB, DK, TIO, NSL, RS, R>::WAVES)) 
           for (int s = 0; s < NSL; ++s)
 #pragma unroll
             for (int hf = 0; hf < 2; ++hf)
-              st[s][hf] = Pair<F>::template mma<false>(op.x[hf][p], xp[s][p], st[s][hf]);
+              st[s][hf] = rows_mma<NB, false>(op.x[hf][p], xp[s][p], st[s][hf]);
         if constexpr (PS == 2)
 #pragma unroll
           for (int s = 0; s < NSL; ++s)
@@ -376,31 +420,45 @@ __global__ __launch_bounds__((64 * StateShape<NB, DK, TIO, NSL, RS, R>::WAVES)) 
 #pragma unroll
           for (int v = 0; v < 4; ++v) Sfin[sidx(s, hf, v)] = st[s][hf][v];
     }
-  } else if (wv < SW + OW) {
-    // ---- output wave: rows of row block I of O; the same barriers
-    const int o_ = wv - SW, I = o_ * RS + rs;
+  } else if (wv >= SH::O0 && wv < SH::O0 + OW) {
+    // ---- output wave: OB row blocks of O; the same barriers
+    const int o_ = wv - SH::O0;
+    // this workgroup's block number of block n of the wave (a first and a last
+    // one: the later the block, the more of P' there is), and the chunk's
+    auto bno = [&](int n) __attribute__((always_inline)) { return n == 0 ? o_ : OB * OW - 1 - o_; };
+    auto blkI = [&](int n) __attribute__((always_inline)) { return bno(n) * RS + rs; };
     const int64_t ldo = (int64_t)H * DV;
-    TIO* ob = O + tokS * ldo + (int64_t)h * DV + 16 * NSL * j + 4 * NSL * gq + (I * 16 + c) * ldo;
+    TIO* ob = O + tokS * ldo + (int64_t)h * DV + 16 * NSL * j + 4 * NSL * gq + c * ldo;
     struct POps {
-      Pair<F> p[2];  // P' row pairs (I, p), p <= I / 2
+      Pair<F> p[OB][2];  // P' row pairs (I, p), p <= I / 2
     };
     auto load_p = [&](POps& op, int64_t ck) __attribute__((always_inline)) {
 #pragma unroll
-      for (int p = 0; p < 2; ++p)
-        if (2 * p <= I) op.p[p] = slot_load<F>(wsP + ck * H * LY::P + pidx(I, p) * 512, l);
+      for (int n = 0; n < OB; ++n)
+#pragma unroll
+        for (int p = 0; p < 2; ++p)
+          if (2 * p <= blkI(n))
+            op.p[n][p] = rows_load<NB, F>(wsP + ck * H * LY::P + pidx(blkI(n), p) * 512, l);
     };
-    Pair<F> qr[NQ];
-    float gr = 0.f;
+    Pair<F> qr[OB][NQ];
+    float gr[OB];
     auto read_rows = [&](int buf) __attribute__((always_inline)) {
 #pragma unroll
-      for (int q = 0; q < NQ; ++q) qr[q] = KR::template pair<F>(sQ[buf], o_ * 16 + c, q, gq);
-      gr = sg[buf][I * 16 + c];
+      for (int n = 0; n < OB; ++n) {
+#pragma unroll
+        for (int q = 0; q < NQ; ++q)
+          qr[n][q] = KR::template pair<F>(sQ[buf], bno(n) * 16 + c, q, gq);
+        gr[n] = sg[buf][blkI(n) * 16 + c];
+      }
     };
     auto compute = [&](const POps& op, int ck, POps& nx, int cknx, int bufnx) __attribute__((always_inline)) {
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int q = 0; q < NQ; ++q) hold(qr[q]);
-      hold(gr);
+      for (int n = 0; n < OB; ++n) {
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) hold(qr[n][q]);
+        hold(gr[n]);
+      }
       lds_barrier();  // state pairs published
       Pair<F> sp[NSL][NQ];
 #pragma unroll
@@ -410,41 +468,49 @@ __global__ __launch_bounds__((64 * StateShape<NB, DK, TIO, NSL, RS, R>::WAVES)) 
       __builtin_amdgcn_sched_barrier(0);
       load_p(nx, cknx);
       __builtin_amdgcn_sched_barrier(0);
-      const float eg = __expf(gr);
-      f32x4 o[NSL];
+      f32x4 o[OB][NSL];
 #pragma unroll
-      for (int s = 0; s < NSL; ++s) o[s] = zero4();
+      for (int n = 0; n < OB; ++n) {
+        const float eg = __expf(gr[n]);
 #pragma unroll
-      for (int q = 0; q < NQ; ++q)
+        for (int s = 0; s < NSL; ++s) o[n][s] = zero4();
 #pragma unroll
-        for (int s = 0; s < NSL; ++s) o[s] = Pair<F>::template mma<true>(qr[q], sp[s][q], o[s]);
+        for (int q = 0; q < NQ; ++q)
 #pragma unroll
-      for (int s = 0; s < NSL; ++s) {
-        o[s] *= eg;
-        hold(o[s]);  // the state pairs are read before the barrier
+          for (int s = 0; s < NSL; ++s)
+            o[n][s] = Pair<F>::template mma<true>(qr[n][q], sp[s][q], o[n][s]);
+#pragma unroll
+        for (int s = 0; s < NSL; ++s) {
+          o[n][s] *= eg;
+          hold(o[n][s]);  // the state pairs are read before the barrier
+        }
       }
       lds_barrier();  // X published; the next chunk's rows are in LDS
       Pair<F> xp[NSL][2];
 #pragma unroll
       for (int p = 0; p < 2; ++p)
-        if (2 * p <= I)
+        if (2 * p <= (OB > 1 ? NB - 1 : blkI(0)))
 #pragma unroll
-          for (int s = 0; s < NSL; ++s) xp[s][p] = slot_load<F>(xv[s] + p * 512, l);
+          for (int s = 0; s < NSL; ++s) xp[s][p] = rows_load<NB, F>(xv[s] + p * 512, l);
       __builtin_amdgcn_sched_barrier(0);
       read_rows(bufnx);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int p = 0; p < 2; ++p)
-        if (2 * p <= I)
+      for (int n = 0; n < OB; ++n) {
+        const int I = blkI(n);
 #pragma unroll
-          for (int s = 0; s < NSL; ++s)
-            o[s] = Pair<F>::template mma<true>(op.p[p], xp[s][p], o[s]);
-      if (!VARLEN || I * 16 + c < rows_of(ck)) {
-        TIO* op_ = ob + (int64_t)ck * C * ldo;
-        if constexpr (NSL == 1)
-          store4(op_, scale * o[0]);
-        else
-          store_row8(op_, scale * o[0], scale * o[1]);
+        for (int p = 0; p < 2; ++p)
+          if (2 * p <= I)
+#pragma unroll
+            for (int s = 0; s < NSL; ++s)
+              o[n][s] = rows_mma<NB, true>(op.p[n][p], xp[s][p], o[n][s]);
+        if (!VARLEN || I * 16 + c < rows_of(ck)) {
+          TIO* op_ = ob + ((int64_t)ck * C + I * 16) * ldo;
+          if constexpr (NSL == 1)
+            store4(op_, scale * o[n][0]);
+          else
+            store_row8(op_, scale * o[n][0], scale * o[n][1]);
+        }
       }
     };
     if (nc > 0) {
@@ -471,7 +537,7 @@ __global__ __launch_bounds__((64 * StateShape<NB, DK, TIO, NSL, RS, R>::WAVES)) 
     // barrier, and it has landed when all but the copies of the R - 1 chunks
     // issued after it have.
     constexpr int LW = SH::LW;
-    const int w = wv - SW - OW;
+    const int w = wv - SH::L0;
     // K and V rows: the inputs, or the workspace's copies of the tile
     const bool copies = !VARLEN && K == nullptr;
     const int64_t krow = copies ? DK : (int64_t)H * DK, vrow = copies ? DV : (int64_t)H * DV;
@@ -579,49 +645,70 @@ hipError_t run_state(const TIO* ws, const TIO* Q, const TIO* K, const TIO* V, co
   const bool packed = pk.cu != nullptr;
   const int64_t BH = (int64_t)(packed ? pk.nseq : B) * H;
   const int cus = compute_units();
-#define GDN_STATE(NSL, RS, R, GD, VL)                                                          \
+#define GDN_STATE(NSL, RS, R, VL)                                                              \
   do {                                                                                         \
     using SH = StateShape<NB, DK, TIO, NSL, RS, R>;                                            \
     constexpr int64_t per = RS * (DV / 16 / NSL), NT = 64 * SH::WAVES;                         \
     constexpr int64_t most = ((int64_t)1 << 31) / (per * NT) / 8 * 8;  /* heads a launch */    \
     for (int64_t bh = 0; bh < BH; bh += most) {                                                \
       const int64_t n = BH - bh < most ? BH - bh : most;                                       \
-      hipLaunchKernelGGL((k_fwd_state<NB, DK, DV, F, TIO, NSL, RS, R, GD, VL>),                \
+      hipLaunchKernelGGL((k_fwd_state<NB, DK, DV, F, TIO, NSL, RS, R, VL>),                    \
                          dim3((unsigned)((n + 7) / 8 * 8 * per)), dim3(NT), 0, st, ws, Q, K,   \
                          V, gam, (int)gtiles, S0, O, Sfin, n_tiles, (int)bh, (int)n, L, H, scale, pk);  \
     }                                                                                          \
+    return hipGetLastError();                                                                  \
   } while (0)
-#define GDN_STATE_V(NSL, RS, R, GD) \
-  do { if (packed) GDN_STATE(NSL, RS, R, GD, true); else GDN_STATE(NSL, RS, R, GD, false); } while (0)
-  // Which shape (us per chunk of 64, dk = dv = 128, MI355X; S_final in place
-  // rules out RS > 1: a workgroup that starts late would read the new state):
-  //   one slice, two workgroups sharing O, while these fit the CUs: bf16 16
-  //     heads 0.62 (one workgroup a slice 0.75; two slices, two sharing 0.72);
-  //     fp32 2.4 (one workgroup a slice 2.9);
-  //   two slices, two workgroups sharing O, while these fit: bf16 32 heads
+#define GDN_STATE_V(NSL, RS, R) \
+  do { if (packed) GDN_STATE(NSL, RS, R, true); else GDN_STATE(NSL, RS, R, false); } while (0)
+  // Which shape (MI355X, dk = dv = 128; S_final in place rules out RS > 1: a
+  // workgroup that starts late would read the new state).
+  // bf16, us per chunk of 64:
+  //   one slice, two workgroups sharing O, while these fit the CUs: 16 heads
+  //     0.62 (one workgroup a slice 0.75; two slices, two sharing 0.72);
+  //   two slices, two workgroups sharing O, while these fit: 32 heads
   //     1.08 (one slice each 1.30, two slices without sharing 1.35);
   //   two slices, no sharing beyond: 64 heads 1.51 (sharing 2.12, one slice
   //     2.57).
+  // fp32, us of the layer at 2048 tokens:
+  //   one slice, two workgroups sharing O, while these fit the CUs: C = 64, 16
+  //     heads 137 (one workgroup a slice 148);
+  //   one slice, one workgroup, while these fit: C = 64, 32 heads 155;
+  //   beyond, a CU has to work on two slices at once or the launch takes two
+  //     rounds.  One workgroup of two slices reads the chunk's operands once for
+  //     both: C = 64, 48 heads 266, one slice each 320; C = 32, dk = 128, 48
+  //     heads 189, 257; C = 16, dk = 128, 48 heads 273, two workgroups of one
+  //     slice a CU 284.  At C = 64, dk = 128 its LDS has room for one chunk, not
+  //     two: the copies of the next one hide behind the products.
+  //   Workgroups of one slice, two or three on a CU, at dk = 64 (dv = 128: C =
+  //     64, 128 heads 386, two slices 403; C = 32, 65 heads 202, 222; C = 16, 64
+  //     heads 171, 200), and where two slices each would just begin another
+  //     round at C = 16 (dk = 128: 65 heads 395, 516; 80 heads 491, 532; 96 heads
+  //     552, 545; dk = 64: 128 heads 325, 324).
   // The ring of two chunks: three and four measured the same.
   const int64_t slices = BH * (DV / 16);
-  const bool share = NB > 1 && !(S0 && S0 == Sfin);
-  constexpr int RS2 = NB > 1 ? 2 : 1;
+  const bool share = !(S0 && S0 == Sfin);
   if constexpr (sizeof(TIO) == 2) {
-    if (2 * slices <= cus && share)
-      GDN_STATE_V(1, RS2, 2, 2);
-    else if (slices <= cus && share)
-      GDN_STATE_V(2, RS2, 2, 2);
+    constexpr int RS2 = NB > 1 ? 2 : 1;
+    if (NB > 1 && 2 * slices <= cus && share)
+      GDN_STATE_V(1, RS2, 2);
+    else if (NB > 1 && slices <= cus && share)
+      GDN_STATE_V(2, RS2, 2);
     else
-      GDN_STATE_V(2, 1, 2, 2);
+      GDN_STATE_V(2, 1, 2);
   } else {
-    if (2 * slices <= cus && share)
-      GDN_STATE_V(1, RS2, 2, 2);
-    else
-      GDN_STATE_V(1, 1, 2, 2);
+    if constexpr (NB > 1)
+      if (2 * slices <= cus && share) GDN_STATE_V(1, 2, 2);
+    if (slices <= cus) GDN_STATE_V(1, 1, 2);
+    if constexpr (NB > 1 && DK == 64) {
+      GDN_STATE_V(1, 1, NB == 4 ? 1 : 2);
+    } else {
+      if constexpr (NB == 1)
+        if (2 * slices <= 5 * cus && (DK == 64 || slices > 2 * cus)) GDN_STATE_V(1, 1, 2);
+      GDN_STATE_V(2, 1, NB * DK <= 256 ? 2 : 1);
+    }
   }
 #undef GDN_STATE_V
 #undef GDN_STATE
-  return hipGetLastError();
 }
 
 #define GDN_STATE_INST(NB, DK, DV)                                                               \

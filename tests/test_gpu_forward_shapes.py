@@ -83,3 +83,47 @@ def test_packed_shapes(C, dt, nseq):
                                            inverse=lambda A: gdn.neumann_inverse(A, N, S))
     check(host(O), Or, dt, "O")
     check(host(Sf), Sr, dt, "S_final")
+
+
+# fp32 past 256 slices: C = 64 as two slices with a ring of one chunk (dk = 128)
+# or one slice with such a ring (dk = 64); C = 32 as two slices (dk = 128) or one
+# with a ring of two; C = 16 as one slice from 512 (dk = 64: 256) to 640 slices
+# and as two on either side
+@pytest.mark.parametrize("C,dk,dv,H", [(64, 128, 128, 33), (64, 128, 64, 66), (64, 64, 128, 34),
+                                       (32, 128, 64, 65), (32, 64, 128, 33), (16, 128, 128, 33),
+                                       (16, 128, 128, 65), (16, 64, 128, 33), (16, 64, 128, 81)])
+def test_fp32_shapes_past_the_compute_units(C, dk, dv, H):
+    test_every_workgroup_shape_gives_the_same_bits(C, dk, dv, H, "f32")
+
+
+@pytest.mark.parametrize("C,H", [(64, 19), (32, 9), (16, 9), (16, 42)])
+def test_packed_fp32_shapes_past_the_compute_units(C, H):
+    # ragged and empty sequences; the small call takes one slice a workgroup
+    rng = np.random.default_rng(H)
+    lengths, d = [2 * C + 1, 1, 0, C], 128
+    cu = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64)
+    T = int(cu[-1])
+    print(f"packed fp32 state pass C={C} H={H}", flush=True)
+    z = rng.standard_normal((2, 1, T, H, d)).astype(np.float32)
+    Q, K = z / np.linalg.norm(z, axis=-1, keepdims=True)
+    V = rng.standard_normal((1, T, H, d)).astype(np.float32)
+    beta = rng.random((1, T, H)).astype(np.float32)
+    g = varlen.varlen_cumsum(-0.1 * rng.random((T, H)), cu, C)[None].astype(np.float32)
+    S0 = rng.standard_normal((len(lengths), H, d, d)).astype(np.float32)
+    tables = G.gdn_varlen_tables(cu, C)
+
+    def part(sl):
+        return G.gdn_chunk_forward_varlen(
+            *(dev(x[:, :, sl], "f32") for x in (Q, K, V)), dev32(beta[:, :, sl]),
+            dev32(g[:, :, sl]), tables, C, S0=dev32(S0[:, sl]))
+
+    O, Sf = part(slice(0, H))
+    o, s = part(slice(H - 2, H))
+    assert torch.equal(O[:, :, H - 2:], o) and torch.equal(Sf[:, H - 2:], s)
+    N, S = gdn.default_order(C)
+    Or, Sr = varlen.forward_varlen_chunked(
+        *(x[:, :, H - 2:].astype(np.float64) for x in (Q, K, V)), beta[:, :, H - 2:],
+        g[:, :, H - 2:], cu, C, S0[:, H - 2:], d ** -0.5,
+        inverse=lambda A: gdn.neumann_inverse(A, N, S))
+    check(host(o), Or, "f32", "O")
+    check(host(s), Sr, "f32", "S_final")

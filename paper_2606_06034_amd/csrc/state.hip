@@ -138,9 +138,10 @@ struct StateShape {
   static constexpr int C = 16 * NB, NQ = DK / 32, NP = npair(NB);
   static constexpr int SWV = NB > NQ ? NB : NQ;  // recurrence waves
   // loader waves: a wave issues a copy of strided rows every 27 ns, a CU takes
-  // one every 10 ns (fp32: two, the registers of a third wave per SIMD are
-  // worth more)
-  static constexpr int LW = sizeof(TIO) == 2 ? 4 : 2;
+  // one every 10 ns.  Two only in fp32 and for the small chunks of dk = 128: a
+  // third wave on a SIMD leaves 168 registers a lane, and 4 to 12 of those
+  // chunks' values went to scratch
+  static constexpr int LW = sizeof(TIO) == 2 && (NB >= 4 || DK == 64) ? 4 : 2;
   // row blocks of O an output wave forms: one, but in fp32 two where more
   // output waves would be the third wave on a SIMD (168 registers a lane: the
   // 189 to 200 of C = 64 did not fit and went to scratch within the chain)
@@ -149,9 +150,10 @@ struct StateShape {
   static constexpr int WAVES = SWV + OW + LW;
   // The first output and loader wave.  Waves go to the four SIMDs in turn; where
   // only the first of four recurrence waves have rows (NB < 4), the loaders come
-  // before the output waves, which then have SIMDs of their own (fp32, us of the
-  // layer at 2048 tokens, 4 heads: C = 32 119 -> 97, C = 16 186 -> 144).
-  static constexpr bool LFIRST = sizeof(TIO) == 4 && SWV == 4 && NB < 4;
+  // before the output waves, which then have SIMDs of their own (us of the
+  // layer at 2048 tokens, 4 heads, fp32: C = 32 119 -> 97, C = 16 186 -> 144;
+  // bf16 within 3 %).
+  static constexpr bool LFIRST = SWV == 4 && NB < 4;
   static constexpr int O0 = SWV + (LFIRST ? LW : 0), L0 = SWV + (LFIRST ? 0 : OW);
   // Workgroups a CU is to hold.  fp32, one slice each without sharing: two
   // where their LDS fits, as the launch rule counts on (run_state).
@@ -662,11 +664,16 @@ hipError_t run_state(const TIO* ws, const TIO* Q, const TIO* K, const TIO* V, co
   do { if (packed) GDN_STATE(NSL, RS, R, true); else GDN_STATE(NSL, RS, R, false); } while (0)
   // Which shape (MI355X, dk = dv = 128; S_final in place rules out RS > 1: a
   // workgroup that starts late would read the new state).
-  // bf16, us per chunk of 64:
+  // bf16, us per chunk of 64 of the state pass, us of the layer at 4096 tokens:
   //   one slice, two workgroups sharing O, while these fit the CUs: 16 heads
   //     0.62 (one workgroup a slice 0.75; two slices, two sharing 0.72);
-  //   two slices, two workgroups sharing O, while these fit: 32 heads
-  //     1.08 (one slice each 1.30, two slices without sharing 1.35);
+  //   two slices, two workgroups sharing O, while these fit, C = 64: 32 heads
+  //     1.08 (one slice each 1.30, two slices without sharing 1.35); C = 32 only
+  //     with dk = 128, dv = 64 (64 heads 116, one slice each 121; dv = 128, 32
+  //     heads 87, 82);
+  //   one slice each while these fit: in place, C = 64, 4 heads 59 (two slices
+  //     65), 32 heads 77 (81); C = 32, 8 heads 67 (84); C = 16, 8 heads 114
+  //     (140), 32 heads 131 (145);
   //   two slices, no sharing beyond: 64 heads 1.51 (sharing 2.12, one slice
   //     2.57).
   // fp32, us of the layer at 2048 tokens:
@@ -688,13 +695,13 @@ hipError_t run_state(const TIO* ws, const TIO* Q, const TIO* K, const TIO* V, co
   const int64_t slices = BH * (DV / 16);
   const bool share = !(S0 && S0 == Sfin);
   if constexpr (sizeof(TIO) == 2) {
-    constexpr int RS2 = NB > 1 ? 2 : 1;
-    if (NB > 1 && 2 * slices <= cus && share)
-      GDN_STATE_V(1, RS2, 2);
-    else if (NB > 1 && slices <= cus && share)
-      GDN_STATE_V(2, RS2, 2);
-    else
-      GDN_STATE_V(2, 1, 2);
+    if constexpr (NB > 1) {
+      if (2 * slices <= cus && share) GDN_STATE_V(1, 2, 2);
+      if constexpr (NB == 4 || (DK == 128 && DV == 64))
+        if (slices <= cus && share) GDN_STATE_V(2, 2, 2);
+    }
+    if (slices <= cus) GDN_STATE_V(1, 1, 2);
+    GDN_STATE_V(2, 1, 2);
   } else {
     if constexpr (NB > 1)
       if (2 * slices <= cus && share) GDN_STATE_V(1, 2, 2);

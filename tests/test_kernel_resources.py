@@ -84,7 +84,7 @@ def per_cu(k):
     return min(160 * 1024 // k[".group_segment_fixed_size"], 4 * min(8, 512 // regs) // waves)
 
 
-@pytest.mark.parametrize("dt", ["f32"])
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
 def test_state_pass_keeps_its_values_in_registers(kernels, dt):
     for shape, k in state_kernels(kernels, dt).items():
         assert k[".vgpr_spill_count"] == 0 and k[".private_segment_fixed_size"] == 0, shape

@@ -28,6 +28,7 @@
 // features of K and Q rows.  Value columns of slice s of a workgroup at
 // column base n0: NSL = 1, n0 + n; NSL = 2, n0 + 8 (n / 4) + 4 s + n % 4, so a
 // lane's 4 columns of both slices are one run of 8.
+#include <atomic>
 #include <type_traits>
 
 #include "forward.hpp"
@@ -626,18 +627,19 @@ __global__ __launch_bounds__((64 * StateShape<NB, DK, TIO, NSL, RS, R>::WAVES),
 
 // ---------------------------------------------------------------------------
 
-// compute units of the current device (cached per device)
+// Compute units of the current device, looked up once per device.  Host threads
+// may ask at the same time: each then stores the same number.
 static int compute_units() {
-  static int cached[64] = {0};
+  static std::atomic<int> cached[64];
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
-  if (!cached[dev]) {
-    int n = 0;
+  int n = cached[dev].load(std::memory_order_relaxed);
+  if (n == 0) {
     if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0)
       n = 256;
-    cached[dev] = n;
+    cached[dev].store(n, std::memory_order_relaxed);
   }
-  return cached[dev];
+  return n;
 }
 
 template <int NB, int DK, int DV, typename F, typename TIO>

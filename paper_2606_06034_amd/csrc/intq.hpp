@@ -55,10 +55,6 @@ __device__ __forceinline__ i32x4 unpack4(int w) {
   return r;
 }
 
-template <int NB>
-__device__ __forceinline__ i32x4 blki(const AccI<NB>& D, int I, int J) {
-  return (J <= I && I < NB) ? D.a[bidx(I, J)] : zero_i4();
-}
 // Quads from blocks; blocks that cannot meet the band [lo, hi] (structurally
 // zero) are packed as constant zeros.
 template <int NB>
@@ -129,10 +125,6 @@ __device__ __forceinline__ void band_blocks(V* a, int lo, int hi) {
         }
       }
     }
-}
-template <int NB, bool COLFORM>
-__device__ __forceinline__ void band_i(AccI<NB>& D, int lo, int hi) {
-  band_blocks<NB, COLFORM>(D.a, lo, hi);
 }
 
 // wave-wide maximum (the device library's DPP reduction), as a scalar

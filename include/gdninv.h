@@ -346,9 +346,10 @@ int gdn_chunk_inverse_neumann_i16_fused(const void* K, const float* beta, const 
  * GDN_BF16); beta, g: [B, L, H] fp32 as for gdn_build_A.  S0 (nullable:
  * zero state) and S_final (nullable: not written): [B, H, dk, dv] fp32;
  * S_final may be S0 itself (updated in place) but must not overlap it
- * otherwise.  bf16 mode rounds to bf16 every MFMA operand, including the
- * state where it multiplies K and Q, and X, P' and G;
- * the state itself is carried in fp32.  workspace: device memory of at least
+ * otherwise.  bf16 mode rounds to bf16 every MFMA operand: the state where it
+ * multiplies K and Q, X, G, P', and of the products that form these two
+ * (Q K^T) (.) D and (T - I) diag(beta), with the unit diagonal's share added
+ * unrounded; the state itself is carried in fp32.  workspace: device memory of at least
  * gdn_chunk_forward_workspace() bytes, owned by the caller, contents
  * undefined on return; it must not overlap any tensor argument.
  * C in {16, 32, 64} (GDN_ERR_UNSUPPORTED for 128).  L = 0 with B H > 0

@@ -7,7 +7,9 @@
 //   D_ij = e^{gamma_i - gamma_j} for i >= j, else 0,
 // the state pass works with the chunk's own K, V and Q and two products of
 // the per-chunk launch,
-//   G = K^T diag(e^{gamma_last - gamma}) T',   P' = P T':
+//   G = K^T diag(e^{gamma_last - gamma}) T',   P' = P T'
+// (formed with (T - I) diag(beta) as the operand; the unit diagonal's share, K^T
+// diag(e^{gamma_last - gamma} beta) and P diag(beta), is added unrounded):
 // with S the [dk, dv] state entering the chunk,
 //   X  = V - diag(e^gamma) K S,
 //   O  = scale (diag(e^gamma) Q S + P' X),
@@ -15,8 +17,8 @@
 // which is the chunk recurrence with V_new = U - W S = T' X (W = T diag(beta
 // e^gamma) K, U = T diag(beta) V) folded into G and P'.  Against a workspace
 // of W, U, K^T and P this moves 22 KB instead of 55 KB per C = 64 chunk (bf16,
-// dk = dv = 128) each way, and a chunk's X is exact but for the products'
-// rounding of K S.
+// dk = dv = 128) each way.  In 16 bits the rounded operands are the state (times K
+// and Q), (T - I) diag(beta), P, and then G, P' and X; K, Q and V enter as given.
 //
 // Workspace parts per chunk tile, in elements of the IO type.  A slot is one
 // pair per lane (64 x 8 elements).

@@ -335,9 +335,9 @@ __device__ __forceinline__ void int128_tile(int wv, const AccI<4>& Lr, int eL,
 
 // The integer inverse at C = 128 from codes (gdn_quantize_tiles_* layout).
 // Both C = 128 kernels are held to two waves per SIMD (amdgpu_waves_per_eu):
-// INT8 then fits its registers exactly, INT16 keeps about 125 values in
-// scratch memory; measured on 16384 tiles, 11-31 % less time than at one
-// wave per SIMD.
+// INT8 then fits its registers exactly, INT16 keeps 60 to 65 values in
+// scratch memory; measured on 16384 tiles (INT16 with products in fp64 and 125
+// values there), 11-31 % less time than at one wave per SIMD.
 template <typename W, int NC, int SC>
 __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(2)))
 void k_neumann_int128(const typename W::Code* __restrict__ Aq,

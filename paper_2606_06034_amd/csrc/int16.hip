@@ -76,10 +76,10 @@ __device__ __forceinline__ void store_i16(const AccI<NB>& Tr, int eTo, int16_t* 
 }
 
 // Two waves per SIMD (amdgpu_waves_per_eu): at C = 64 the engine would take 32
-// registers more than the 256 that allows; held to 256 the compiler keeps
-// about 80 values in scratch memory, most of them across the branches that
-// seldom run, and the second wave hides more latency than they cost (one
-// launch from K, 32768 tiles: 499 us against 646 us with one wave).
+// registers more than the 256 that allows; held to 256 the compiler keeps 72
+// values in scratch memory (68 in the launch from K), most of them across the
+// branches that seldom run, and the second wave hides more latency than they
+// cost (the launch from K, 32768 tiles: 516 us against 646 us with one wave).
 template <int NB, bool PLAIN, int NC = -1, int SC = -1>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2)))
 void k_neumann_i16(const int16_t* __restrict__ Aq,
@@ -112,7 +112,7 @@ void k_neumann_i16(const int16_t* __restrict__ Aq,
 
 // The whole INT16 path for one chunk in one wave: A in fp32 from K, beta, g
 // (the values gdn_build_A writes), quantised in registers, then the integer
-// inverse.  Bound by vector operations: 32768 tiles of C = 64 in 514 us on
+// inverse.  Bound by vector operations: 32768 tiles of C = 64 in 516 us on
 // MI355X, against 885 us with products and sums as fp64 integers at one wave
 // per SIMD.
 template <int NB, int DK, typename F, typename TK, int NC = -1, int SC = -1>

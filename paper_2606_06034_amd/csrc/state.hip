@@ -14,10 +14,10 @@
 // through its L1.  Measured on MI355X, a wave load of 1 KB costs a CU 9 ns
 // when consecutive lanes read consecutive 16 bytes of whole rows, and 31 ns in
 // the fragment order (lane (g, c): row c, 16 bytes at 8g), where each group of
-// 16 lanes touches 16 rows.  So two loader waves copy K, Q, V and the gates of
-// the chunks ahead into LDS rows by DMA in row order, and the fragments are
-// read from there; G and P' lie in the workspace as fragments and come
-// straight into a ring of registers.
+// 16 lanes touches 16 rows.  So loader waves (two or four) copy K, Q, V and the
+// gates of the chunks ahead into LDS rows by DMA in row order, and the fragments
+// are read from there; G and P' lie in the workspace as fragments and come
+// straight into registers.
 //
 // Fragment conventions (tile16.hpp): a pair over 16-blocks {2p, 2p + 1}
 // gives slot s of lane (g, c) the index 32p + 16 (s / 4) + 4g + s % 4; a
@@ -693,7 +693,8 @@ hipError_t run_state(const TIO* ws, const TIO* Q, const TIO* K, const TIO* V, co
   //     heads 171, 200), and where two slices each would just begin another
   //     round at C = 16 (dk = 128: 65 heads 395, 516; 80 heads 491, 532; 96 heads
   //     552, 545; dk = 64: 128 heads 325, 324).
-  // The ring of two chunks: three and four measured the same.
+  // The ring (R) of two chunks: three and four measured the same; one where two
+  // do not fit the LDS that the workgroups of a CU share.
   const int64_t slices = BH * (DV / 16);
   const bool share = !(S0 && S0 == Sfin);
   if constexpr (sizeof(TIO) == 2) {

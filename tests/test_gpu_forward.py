@@ -6,9 +6,9 @@ storage dtype, upcast to float64) with the same inverse (exact, or T_hat(N,
 S) at the order the GPU uses).  Tolerance: max |O - O_ref| and
 max |S - S_ref| within TOL * max(1, max |ref|), TOL = 1e-5 in fp32 mode
 and 2e-2 in bf16 mode, the bounds the inverse itself is held to; in bf16
-every MFMA operand is rounded (W, U, P, the state where it multiplies W and
-Q, V_new where it multiplies P and K^T), each a relative 2^-9, and the
-output sums a handful of such products.
+every MFMA operand is rounded (the state where it multiplies K and Q; X = V -
+e^g K S; P and (T - I) diag(beta), whose product is P'; P' and G, which multiply
+X), each a relative 2^-9, and the output sums a handful of such products.
 """
 
 import numpy as np

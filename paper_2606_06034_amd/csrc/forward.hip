@@ -243,8 +243,10 @@ __global__ __launch_bounds__(64) void k_fwd_chunk(const TIO* __restrict__ Q,
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
           const int i = I * 16 + ln.c(), j = J * 16 + 4 * ln.g() + v;
-          const float x = Pm.a[bidx(I, J)][v];
-          Pm.a[bidx(I, J)][v] = (i >= j) ? x * __expf(sg[i] - sg[j]) : 0.f;
+          // formed either way, then chosen: a branch around each of the diagonal
+          // blocks' exponentials would keep the others from overlapping
+          const float x = Pm.a[bidx(I, J)][v] * __expf(sg[i] - sg[j]);
+          Pm.a[bidx(I, J)][v] = I > J || i >= j ? x : 0.f;
         }
     RowP<NB, F> PR;
     to_rowp(PR, Pm);

@@ -144,8 +144,10 @@ struct StateShape {
   // chunks' values went to scratch
   static constexpr int LW = sizeof(TIO) == 2 && (NB >= 4 || DK == 64) ? 4 : 2;
   // row blocks of O an output wave forms: one, but in fp32 two where more
-  // output waves would be the third wave on a SIMD (168 registers a lane: the
-  // 189 to 200 of C = 64 did not fit and went to scratch within the chain)
+  // output waves would be the third wave on a SIMD: two slices take 200
+  // registers a lane of the 168 that leaves; one slice fits, and is slower all
+  // the same (us of the layer at 2048 tokens, C = 64, 17 heads 151 against 148;
+  // dk = 64, 32 heads 131 against 107)
   static constexpr int OB = sizeof(TIO) == 4 && SWV + NB / RS + LW > 8 ? 2 : 1;
   static constexpr int OW = NB / RS / OB;  // output waves
   static constexpr int WAVES = SWV + OW + LW;

@@ -477,16 +477,20 @@ __global__ __launch_bounds__((64 * StateShape<NB, DK, TIO, NSL, RS, R>::WAVES),
 #pragma unroll
       for (int n = 0; n < OB; ++n) {
         const float eg = __expf(gr[n]);
+        f32x4 qs[NSL][PS];
 #pragma unroll
-        for (int s = 0; s < NSL; ++s) o[n][s] = zero4();
+        for (int s = 0; s < NSL; ++s)
+#pragma unroll
+          for (int u = 0; u < PS; ++u) qs[s][u] = zero4();
 #pragma unroll
         for (int q = 0; q < NQ; ++q)
 #pragma unroll
           for (int s = 0; s < NSL; ++s)
-            o[n][s] = Pair<F>::template mma<true>(qr[n][q], sp[s][q], o[n][s]);
+            qs[s][q % PS] = Pair<F>::template mma<true>(qr[n][q], sp[s][q], qs[s][q % PS]);
 #pragma unroll
         for (int s = 0; s < NSL; ++s) {
-          o[n][s] *= eg;
+          if constexpr (PS == 2) qs[s][0] += qs[s][1];
+          o[n][s] = eg * qs[s][0];
           hold(o[n][s]);  // the state pairs are read before the barrier
         }
       }
@@ -503,12 +507,22 @@ __global__ __launch_bounds__((64 * StateShape<NB, DK, TIO, NSL, RS, R>::WAVES),
 #pragma unroll
       for (int n = 0; n < OB; ++n) {
         const int I = blkI(n);
+        // (fp32: the share of the state is added last)
+        f32x4 first[NSL];
+#pragma unroll
+        for (int s = 0; s < NSL; ++s) {
+          first[s] = o[n][s];
+          if constexpr (PS == 2) o[n][s] = zero4();
+        }
 #pragma unroll
         for (int p = 0; p < 2; ++p)
           if (2 * p <= I)
 #pragma unroll
             for (int s = 0; s < NSL; ++s)
               o[n][s] = rows_mma<NB, true>(op.p[n][p], xp[s][p], o[n][s]);
+        if constexpr (PS == 2)
+#pragma unroll
+          for (int s = 0; s < NSL; ++s) o[n][s] += first[s];
         if (!VARLEN || I * 16 + c < rows_of(ck)) {
           TIO* op_ = ob + ((int64_t)ck * C + I * 16) * ldo;
           if constexpr (NSL == 1)

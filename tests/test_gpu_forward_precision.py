@@ -12,7 +12,7 @@ from entry to entry do not.  (T diag(beta) as an operand of G and P': 1.11 and
 1.16 times the bound on O at C = 64; beta and the unit diagonal outside the
 rounded operands: 0.89 and 0.91.)  fp32: drawn and constant beta; the longer
 chain of products makes up for its roundings by adding the largest terms last
-and the product with the state in two halves (0.52 to 0.93 of the bounds; 1.01
+and the products with the state in two halves (0.54 to 0.90 of the bounds; 1.01
 to 1.11 without)."""
 
 import numpy as np
